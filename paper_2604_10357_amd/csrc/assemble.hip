@@ -200,7 +200,7 @@ constexpr int stage_elems() { return (kStageThreads - 1) / Rule::NQ + 2; }
 
 template <class Rule, typename R>
 constexpr size_t stage_lds_bytes() {
-  const size_t nodal = (size_t)stage_elems<Rule>() * Rule::NEN * 6 * sizeof(double);
+  const size_t nodal = (size_t)stage_elems<Rule>() * nodal_doubles<Rule>() * sizeof(double);
   const size_t trans = (size_t)kStageThreads * (128 + 16);
   return nodal > trans ? nodal : trans;
 }
@@ -221,15 +221,21 @@ __device__ __forceinline__ void stage_tile(const AsmArgs& a, R* stage, int64_t b
   const bool act = p < npts;
   // 1. nodal values of the elements the block's points belong to
   double* nod = reinterpret_cast<double*>(smem);
+  double* terms = nod + EB * NEN * 6;
   gather_nodal<Rule>(a, e_lo, EB, nod);
   __syncthreads();
+  if constexpr (Rule::MC == 1) {
+    t10_element_terms<2, 6>(nod, EB, terms);
+    __syncthreads();
+  }
   // 2. kinematics at the lane's point (lanes past the end evaluate the last
   //    point and store nothing)
   const int64_t pc = act ? p : npts - 1;
   const int64_t e = pc / NQ;
   const int q = (int)(pc - e * NQ);
   double Jinv[9], det, Hd[9], Fd[9];
-  tile_kinematics<Rule>(a, nod + 6 * NEN * (int)(e - e_lo), e, q, Jinv, det, Hd, Fd);
+  const int el = (int)(e - e_lo);
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e, q, Jinv, det, Hd, Fd);
   __syncthreads();  // the nodal values are consumed: the LDS becomes the transpose buffers
   PointOut<R> o;
   const unsigned fl = point_update<R, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
@@ -868,7 +874,7 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
   __shared__ __align__(16) float dn[NEN * kDnL];  // parent gradients of every node at every point
   __shared__ int32_t pos[SYM ? 1 : EB * NEN];     // incidence position of every (element, node)
   __shared__ __align__(16) float stage_buf[(kRowThreads / 64) * (SYM ? NEN : kRowStage) * kStgL];  // per-wave blocks
-  static_assert(EB * NEN * 6 * sizeof(double) <= sizeof(rec), "nodal values fit the record area");
+  static_assert(EB * nodal_doubles<Rule>() * sizeof(double) <= sizeof(rec), "nodal values fit the record area");
   const int tid = threadIdx.x;
   const int64_t e0 = blk * EB;
   const int ne = (int)(a.n_elem - e0 < EB ? a.n_elem - e0 : EB);
@@ -879,11 +885,14 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
     for (int idx = tid; idx < ne * NEN; idx += kRowThreads) pos[idx] = incpos[e0 * NPN + idx];
   for (int idx = tid; idx < NEN * 16; idx += kRowThreads) dn[kDnL * (idx / 16) + idx % 16] = Rule::template rows<float>(idx / 16)[idx % 16];
   __syncthreads();
+  double* terms = nod + EB * NEN * 6;
+  t10_element_terms<2, 6>(nod, ne, terms);
+  __syncthreads();
   const bool act = tid < ne * NQ;
   const int pl = act ? tid : 0;  // idle lanes evaluate point 0 and store nothing
   const int el = pl / NQ, q = pl - el * NQ;
   double Jinv[9], det, Hd[9], Fd[9];
-  tile_kinematics<Rule>(a, nod + 6 * NEN * el, e0 + el, q, Jinv, det, Hd, Fd);
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e0 + el, q, Jinv, det, Hd, Fd);
   __syncthreads();  // the nodal values are consumed: the LDS holds the records from here on
   // 2. the point's record (slot layout of the records above) into LDS
   PointOut<float> o;
@@ -1365,7 +1374,7 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
   const int pl = act ? tid : 0;  // idle lanes evaluate point 0 and store nothing
   const int el = pl / NQ, q = pl - el * NQ;
   double Jinv[9], det, Hd[9], Fd[9];
-  tile_kinematics<Rule>(a, nod + 6 * NEN * el, e0 + el, q, Jinv, det, Hd, Fd);
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, nullptr, e0 + el, q, Jinv, det, Hd, Fd);
   __syncthreads();  // the nodal values are consumed: the LDS holds the records from here on
   PointOut<float> o;
   const unsigned fl = point_update<float, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
@@ -1574,15 +1583,22 @@ __global__ __launch_bounds__(512) void k_gather_rows_mc_batch(BatchArgs b) {
 // node-sorted incidence position of (element, node of a), 3 MC values per
 // incidence.  Pass 2 adds each pattern node's incidence blocks in a fixed order,
 // a lane per row of f, in float64: no atomics, the same sums on every call.
+// Bound by instruction issue (about 900 per point, a third of them float64).
+// 480,000 T10, mixed: 0.156 ms a call with the kinematics as a sum over ten
+// nodes (132 VGPRs), 0.115 ms with the element terms of kernel_common.h (108
+// VGPRs, four waves per SIMD).
 constexpr int kForceThreads = 256;
 template <class Rule>
 constexpr int force_elems() { return kForceThreads / Rule::NQ; }
+// waves per SIMD the registers allow without spilling
+template <class Rule, typename R>
+constexpr int force_min_waves() { return sizeof(R) == 4 && Rule::NEN <= 10 ? 4 : 3; }
 
 template <class Rule, typename R>
-__global__ __launch_bounds__(kForceThreads) void k_elem_force(AsmArgs a, const int32_t* __restrict__ incpos,
+__global__ __launch_bounds__(kForceThreads, (force_min_waves<Rule, R>())) void k_elem_force(AsmArgs a, const int32_t* __restrict__ incpos,
                                                              R* __restrict__ blocks) {
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, MC = Rule::MC, EB = force_elems<Rule>();
-  constexpr size_t NOD = (size_t)EB * NEN * 6 * sizeof(double), PH = (size_t)EB * NQ * 9 * sizeof(R);
+  constexpr size_t NOD = (size_t)EB * nodal_doubles<Rule>() * sizeof(double), PH = (size_t)EB * NQ * 9 * sizeof(R);
   __shared__ __align__(16) unsigned char smem[NOD > PH ? NOD : PH];
   __shared__ R dn[NQ * NEN * 3];  // unit-scaled parent gradients, dN_a(q)_m at 3 (NEN q + a) + m
   const int tid = threadIdx.x;
@@ -1595,11 +1611,16 @@ __global__ __launch_bounds__(kForceThreads) void k_elem_force(AsmArgs a, const i
     dn[idx] = (R)Rule::dN_rt(q, r / 3, r % 3);
   }
   __syncthreads();
+  double* terms = nod + EB * NEN * 6;
+  if constexpr (MC == 1) {
+    t10_element_terms<2, 6>(nod, ne, terms);
+    __syncthreads();
+  }
   const bool act = tid < ne * NQ;
   const int pl = act ? tid : 0;  // idle lanes evaluate point 0 and store nothing
   const int el = pl / NQ, q = pl - el * NQ;
   double Jinv[9], det, Hd[9], Fd[9];
-  tile_kinematics<Rule, true>(a, nod + 6 * NEN * el, e0 + el, q, Jinv, det, Hd, Fd);
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e0 + el, q, Jinv, det, Hd, Fd);
   __syncthreads();  // the nodal values are consumed: the LDS holds Phat from here on
   PointOut<R> o;
   const MatParams mp = launch_material(a);

@@ -107,9 +107,60 @@ __device__ __forceinline__ void gather_nodal(const AsmArgs& a, int64_t e_lo, int
   }
 }
 
-#ifndef TLFEA_KIN_UNROLL
-#define TLFEA_KIN_UNROLL 4
-#endif
+// Parent gradients D = sum_a u_a (x) dN_a of T10 fields at the points of the
+// five-point rule.  With u_cb the value of the node on edge (c, b) and u_cc that
+// of corner c, the gradient at barycentric coordinates L is
+//   D_k = g_k - g_0,  g_b = 4 sum_c L_c u_cb - u_b,
+// and at the rule's points (the centroid, or L_c = 1/2 and the others 1/6)
+//   centroid:          D_k = S_k,
+//   point of corner c: D_k = 4/3 (u_ck - u_c0) + V_k,  V_k = 2/3 S_k - 1/3 (u_k - u_0),
+//   S_k = sum over j other than 0, k of (u_jk - u_j0).
+// V and S belong to the element and are formed once for it (18 values a field,
+// V at 3 i + k, S at 9 + 3 i + k), so a point takes 18 operations a field
+// instead of the 120 of the sum over ten nodes, and no gradient table; every
+// term is a difference of two of the element's values, so no digits go to its
+// rigid displacement.
+constexpr int kT10Terms = 18;
+
+// LDS doubles per element of the gathered fields u and qdot (and their terms)
+template <class Rule>
+constexpr int nodal_doubles() { return 6 * Rule::NEN + (Rule::MC == 1 ? 2 * kT10Terms : 0); }
+
+// V and S of NF fields of `ne` elements: field f of element e at u + STRIDE * 10 e + 3 f
+// (STRIDE doubles per node), the terms at terms + kT10Terms * (NF e + f).
+// Called by every lane of the workgroup, between two barriers.
+template <int NF, int STRIDE>
+__device__ __forceinline__ void t10_element_terms(const double* u, int ne, double* terms) {
+  for (int t = threadIdx.x; t < ne * 3 * NF; t += blockDim.x) {
+    const int e = t / (3 * NF), r = t - 3 * NF * e;  // r = 3 f + i
+    const double* n = u + STRIDE * 10 * e + r;
+    const double u0 = n[0], e01 = n[4 * STRIDE], e12 = n[5 * STRIDE], e02 = n[6 * STRIDE], e03 = n[7 * STRIDE],
+                 e13 = n[8 * STRIDE], e23 = n[9 * STRIDE];
+    const double S[3] = {(e12 - e02) + (e13 - e03), (e12 - e01) + (e23 - e03), (e13 - e01) + (e23 - e02)};
+    double* out = terms + kT10Terms * (t / 3) + 3 * (t % 3);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      out[k] = 2.0 / 3.0 * S[k] - 1.0 / 3.0 * (n[(k + 1) * STRIDE] - u0);
+      out[9 + k] = S[k];
+    }
+  }
+}
+
+// D of one field at point q, u the field's values of the element (STRIDE doubles per node)
+template <int STRIDE>
+__device__ __forceinline__ void t10_parent_gradient(const double* u, const double* terms, int q, double (&D)[9]) {
+  // nodes (c, 0), (c, 1), (c, 2), (c, 3) of the point's corner c = q - 1, four bits each
+  const int row = q <= 1 ? 0x7640 : q == 2 ? 0x8514 : q == 3 ? 0x9256 : 0x3987;
+  const double w = q == 0 ? 0.0 : 4.0 / 3.0;
+  const double* T = terms + (q == 0 ? 9 : 0);
+  const double* c0 = u + STRIDE * (row & 15);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const double* ck = u + STRIDE * ((row >> (4 * (k + 1))) & 15);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) D[3 * i + k] = w * (ck[i] - c0[i]) + T[3 * i + k];
+  }
+}
 
 // Displacement and velocity gradients at point q of element e from its nodal
 // values in LDS (ne: 6 doubles per coefficient): Hd = sum_a u_a (x) g_a,
@@ -118,47 +169,42 @@ __device__ __forceinline__ void gather_nodal(const AsmArgs& a, int64_t e_lo, int
 // first coefficient's values may be taken out of every position coefficient:
 // the terms then stay of the size of the element's own deformation instead of
 // its rigid displacement (a body turned far from the origin keeps the digits
-// of its strain).
-// PART: coefficients in steps of TLFEA_KIN_UNROLL instead of all at once (a
-// full unroll keeps every table load in flight; for the shell's 16
-// coefficients that caps the kernels at one wave per SIMD).  Measured per
-// kernel: steps for the four-coefficient elements (shell and beam) everywhere
-// and for the T10 force and backward kernels, a full unroll for the T10
-// element rows and point records.
-template <class Rule, bool PART = (Rule::MC == 4 || Rule::NEN > 10)>
-__device__ __forceinline__ void tile_kinematics(const AsmArgs& a, const double* ne, int64_t e, int q,
+// of its strain).  T10 takes the closed form above (terms: the element's V and
+// S of both fields; other elements ignore it).  The four-coefficient
+// elements run over the coefficients in steps of four (a full unroll keeps
+// every table load in flight, which costs the shell half its waves) and skip
+// the parent gradients that vanish at every point (Rule::grad_nz).
+template <class Rule>
+__device__ __forceinline__ void tile_kinematics(const AsmArgs& a, const double* ne, const double* terms, int64_t e, int q,
                                                 double (&Jinv)[9], double& det, double (&Hd)[9], double (&Fd)[9]) {
   constexpr int NEN = Rule::NEN;
-  double sc[4];
   load_geometry<Rule>(a, e, q, Jinv, det);
-  element_scales<Rule>(a, e, sc);
-  double Du[9], Dv[9], r0[6];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) Du[t] = Dv[t] = 0.0;
-#pragma unroll
-  for (int t = 0; t < 6; ++t) r0[t] = ne[t];
-  auto add = [&](int al) __attribute__((always_inline)) {
-    const double s = sc[al % 4];
-    const double w0 = Rule::dN_rt(q, al, 0) * s, w1 = Rule::dN_rt(q, al, 1) * s, w2 = Rule::dN_rt(q, al, 2) * s;
-    const bool position = Rule::MC == 1 || (al & 3) == 0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const double u = ne[6 * al + i] - (position ? r0[i] : 0.0);
-      const double v = ne[6 * al + 3 + i] - (position ? r0[3 + i] : 0.0);
-      Du[3 * i] += u * w0;
-      Du[3 * i + 1] += u * w1;
-      Du[3 * i + 2] += u * w2;
-      Dv[3 * i] += v * w0;
-      Dv[3 * i + 1] += v * w1;
-      Dv[3 * i + 2] += v * w2;
-    }
-  };
-  if constexpr (PART) {
-#pragma unroll TLFEA_KIN_UNROLL
-    for (int al = 0; al < NEN; ++al) add(al);
+  double Du[9], Dv[9];
+  if constexpr (Rule::MC == 1) {
+    t10_parent_gradient<6>(ne, terms, q, Du);
+    t10_parent_gradient<6>(ne + 3, terms + kT10Terms, q, Dv);
   } else {
+    double sc[4], r0[6];
+    element_scales<Rule>(a, e, sc);
 #pragma unroll
-    for (int al = 0; al < NEN; ++al) add(al);
+    for (int t = 0; t < 9; ++t) Du[t] = Dv[t] = 0.0;
+#pragma unroll
+    for (int t = 0; t < 6; ++t) r0[t] = ne[t];
+#pragma unroll 4
+    for (int al = 0; al < NEN; ++al) {
+      const double s = sc[al % 4];
+      const bool position = (al & 3) == 0;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        if (!Rule::grad_nz(al, m)) continue;
+        const double w = Rule::dN_rt(q, al, m) * s;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          Du[3 * i + m] += (ne[6 * al + i] - (position ? r0[i] : 0.0)) * w;
+          Dv[3 * i + m] += (ne[6 * al + 3 + i] - (position ? r0[3 + i] : 0.0)) * w;
+        }
+      }
+    }
   }
 #pragma unroll
   for (int i = 0; i < 3; ++i)

@@ -244,9 +244,10 @@ __device__ __forceinline__ unsigned point_update(const MatParams& mp, const doub
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         o.M[t] += a_ * Sv[t];
-        o.N[t] += a_ * eta * FFd[t] + b_ * eta * B[t];
-        o.W[t] += a_ * lv * Fd[t] + b_ * lv * F[t];
-        o.Y[t] += a_ * eta * Fd[t] + b_ * eta * F[t];
+        // spelled out: which of the two products is fused must not hang on the code around it
+        o.N[t] += fma(a_ * eta, FFd[t], b_ * eta * B[t]);
+        o.W[t] += fma(a_ * lv, Fd[t], b_ * lv * F[t]);
+        o.Y[t] += fma(a_ * eta, Fd[t], b_ * eta * F[t]);
       }
     }
   }

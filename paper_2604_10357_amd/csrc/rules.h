@@ -59,7 +59,7 @@ struct RuleT10 {
   }
   static constexpr double dN(int q, int a, int m) { return kT10.dN[q][a][m]; }
   __device__ static double dN_rt(int q, int a, int m) { return c_t10.dN[q][a][m]; }
-  __device__ static double w_rt(int q) { return c_t10.w[q]; }
+  __device__ static double w_rt(int q) { return q == 0 ? kT10.w[0] : kT10.w[1]; }  // points 1 .. 4 share a weight
 };
 
 // Float copies of the ANCF gradient tables (element-row kernels, float32
@@ -87,6 +87,8 @@ struct RuleAncf {
     if constexpr (NX == 3) return kAncf332; else return kAncf443;
   }
   static constexpr double dN(int q, int a, int m) { return tab().dS[q][a][m]; }
+  // only the transverse function (kind 3) varies along zeta
+  static constexpr bool grad_nz(int a, int m) { return m < 2 || (a & 3) == 3; }
   __device__ static const AncfTable<NX, NY, NZ>& ctab() {
     if constexpr (NX == 3) return c_a332; else return c_a443;
   }
@@ -101,6 +103,8 @@ struct RuleAncf {
 struct RuleBeam {
   static constexpr int NEN = 8, NPN = 2, MC = 4, NQ = 12;
   static constexpr double dN(int q, int a, int m) { return kBeam322.dS[q][a][m]; }
+  // r and r_x vary along the axis only, r_y also along eta, r_z also along zeta
+  static constexpr bool grad_nz(int a, int m) { return m == 0 || (a & 3) == m + 1; }
   __device__ static double dN_rt(int q, int a, int m) { return c_b322.dS[q][a][m]; }
   __device__ static double w_rt(int q) { return c_b322.w[q]; }
   __device__ static float dNf_rt(int q, int a, int m) { return c_b322_f.v[q][a][m]; }

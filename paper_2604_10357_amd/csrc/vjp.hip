@@ -32,12 +32,13 @@ constexpr int vjp_elems() { return kVjpThreads / Rule::NQ; }
 
 // QD: the qdot product is formed too (bqd non-null)
 template <class Rule, bool QD>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_elem(AsmArgs a, const double* __restrict__ w,
+__global__ __launch_bounds__(kVjpThreads, (Rule::MC == 1 ? 2 : 1)) void k_vjp_elem(AsmArgs a, const double* __restrict__ w,
                                                          const int32_t* __restrict__ incpos, double* __restrict__ bq,
                                                          double* __restrict__ bqd, double* __restrict__ gpart) {
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, MC = Rule::MC, EB = vjp_elems<Rule>();
   constexpr int ZS = QD ? 18 : 9;  // LDS values per point: Zhat of q, then of qdot
-  constexpr size_t NOD = (size_t)EB * NEN * 9 * sizeof(double), ZB = (size_t)EB * NQ * ZS * sizeof(double);
+  constexpr int ND = 9 * NEN + (MC == 1 ? 3 * kT10Terms : 0);  // LDS doubles per element: u, qdot, w (and their terms)
+  constexpr size_t NOD = (size_t)EB * ND * sizeof(double), ZB = (size_t)EB * NQ * ZS * sizeof(double);
   __shared__ __align__(16) unsigned char smem[NOD > ZB ? NOD : ZB];
   __shared__ double dn[NQ * NEN * 3];  // unit-scaled parent gradients, dN_a(q)_m at 3 (NEN q + a) + m
   __shared__ double red[kVjpThreads / 64][5];
@@ -46,6 +47,8 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_elem(AsmArgs a, const doubl
   const int ne = (int)(a.n_elem - e0 < EB ? a.n_elem - e0 : EB);
   double* nod = reinterpret_cast<double*>(smem);  // 6 per coefficient (u, qdot)
   double* wn = nod + EB * NEN * 6;                // 3 per coefficient (w)
+  double* terms = wn + EB * NEN * 3;              // T10: two fields' terms per element, then w's
+  double* wterms = terms + EB * 2 * kT10Terms;
   // u = q - X, qdot and w of every (element, coefficient), all loads of one
   // coefficient issued together
   for (int idx = tid; idx < ne * NEN; idx += kVjpThreads) {
@@ -71,31 +74,39 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_elem(AsmArgs a, const doubl
     dn[idx] = Rule::dN_rt(q, r / 3, r % 3);
   }
   __syncthreads();
+  if constexpr (MC == 1) {
+    t10_element_terms<2, 6>(nod, ne, terms);
+    t10_element_terms<1, 3>(wn, ne, wterms);
+    __syncthreads();
+  }
   const bool act = tid < ne * NQ;
   const int pl = act ? tid : 0;  // idle lanes evaluate point 0 and store nothing
   const int el = pl / NQ, q = pl - el * NQ;
   double Jinv[9], det, Hd[9], Fd[9], Wg[9];
-  tile_kinematics<Rule, true>(a, nod + 6 * NEN * el, e0 + el, q, Jinv, det, Hd, Fd);
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e0 + el, q, Jinv, det, Hd, Fd);
   {
     // W = sum_a w_a (x) g_a, the first position coefficient's value taken out
     // of every position coefficient (the position gradients sum to zero)
-    double sc[4], D[9];
-    element_scales<Rule>(a, e0 + el, sc);
+    double D[9];
     const double* we = wn + 3 * NEN * el;
-    const double r0[3] = {we[0], we[1], we[2]};
+    if constexpr (MC == 1) {
+      t10_parent_gradient<3>(we, wterms + kT10Terms * el, q, D);
+    } else {
+      double sc[4];
+      element_scales<Rule>(a, e0 + el, sc);
+      const double r0[3] = {we[0], we[1], we[2]};
 #pragma unroll
-    for (int t = 0; t < 9; ++t) D[t] = 0.0;
-    for (int al = 0; al < NEN; ++al) {
-      const double s = sc[al % 4];
-      const bool position = MC == 1 || (al & 3) == 0;
-      const double* d = dn + 3 * (NEN * q + al);
-      const double w0 = d[0] * s, w1 = d[1] * s, w2 = d[2] * s;
+      for (int t = 0; t < 9; ++t) D[t] = 0.0;
+#pragma unroll 4
+      for (int al = 0; al < NEN; ++al) {
+        const bool position = (al & 3) == 0;
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const double v = we[3 * al + i] - (position ? r0[i] : 0.0);
-        D[3 * i] += v * w0;
-        D[3 * i + 1] += v * w1;
-        D[3 * i + 2] += v * w2;
+        for (int m = 0; m < 3; ++m) {
+          if (!Rule::grad_nz(al, m)) continue;
+          const double wm = dn[3 * (NEN * q + al) + m] * sc[al % 4];
+#pragma unroll
+          for (int i = 0; i < 3; ++i) D[3 * i + m] += (we[3 * al + i] - (position ? r0[i] : 0.0)) * wm;
+        }
       }
     }
 #pragma unroll
