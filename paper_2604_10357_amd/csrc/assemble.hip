@@ -33,6 +33,7 @@
 #include <cstdlib>
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #include "kernel_common.h"
@@ -105,11 +106,11 @@ __global__ __launch_bounds__(256) void k_stage(AsmArgs a, R* stage) {
 }
 
 // Value W of a tangent record (W is a compile-time index into the layout above).
-template <int W, typename R>
+template <int W, class FO, typename R>
 __device__ __forceinline__ R record_value(const HatOut<R>& h) {
   if constexpr (W < 9 * kSlot) {
     constexpr int slot = W / kSlot, x = W % kSlot, i = slot / 3, k = slot % 3;
-    if constexpr (x < 9) return hat_entry(h, i, x / 3, k, x % 3);
+    if constexpr (x < 9) return hat_entry<FO>(h, i, x / 3, k, x % 3);
     else return h.P[3 * i + k];
   } else {
     return R(0);
@@ -257,7 +258,7 @@ __device__ __forceinline__ void stage_tile(const AsmArgs& a, R* stage, int64_t b
       sfor<0, PER>([&](auto xc) __attribute__((always_inline)) {
         constexpr int x = decltype(xc)::value;
         if constexpr (SYM) v[x] = record_value_sym<ch * CW + j * PER + x>(h);
-        else v[x] = record_value<ch * CW + j * PER + x>(h);
+        else v[x] = record_value<ch * CW + j * PER + x, FuseOther>(h);
       });
       *reinterpret_cast<V*>(tb + lane * LS + j * PER) = v;
     });
@@ -336,7 +337,7 @@ __device__ __forceinline__ void contract_point(const Slot<R, KREC>& s, R d0, R d
   if constexpr (WANT_K) {
     R tn[3];
 #pragma unroll
-    for (int n = 0; n < 3; ++n) tn[n] = s.v[n] * d0 + s.v[3 + n] * d1 + s.v[6 + n] * d2;
+    for (int n = 0; n < 3; ++n) tn[n] = sum3<false>(s.v[n], d0, s.v[3 + n], d1, s.v[6 + n], d2);
     sfor<0, Rule::NEN>([&](auto bc) __attribute__((always_inline)) {
       constexpr int b = decltype(bc)::value;
       constexpr double c0 = Rule::dN(Q, b, 0), c1 = Rule::dN(Q, b, 1), c2 = Rule::dN(Q, b, 2);
@@ -753,26 +754,29 @@ __global__ __launch_bounds__(512) void k_gather_batch(BatchArgs b) {
 }
 
 // ---------------------------------------------------------------------------
-// element rows (T10, float32, with the tangent)
+// element rows (T10, with the tangent)
 // ---------------------------------------------------------------------------
-// Pass 1 reduces over the points itself.  A workgroup computes the records of
-// kRowElems whole elements into LDS (a lane per point, as above), then a lane
-// per task (element, node a, row i, component k) contracts the element's five
-// records exactly as the gather does, giving the ten entries
-// K_e[3a+i][3b+k], b = 0..9, summed over the points in float32 (Sec. 4.4.2,
-// Eq. tangent_block), and its part P_ik dN_a,k of f_a,i (Eq. fint_local).
-// Each (element, node) row block goes to the node's place in the node-sorted
-// incidence list, so that pass 2 reads the blocks of a node range as one
-// contiguous run, each block once, instead of re-reading per-point records
-// for every range that shares an element.
-constexpr int kRowBlk = 96;       // block: K entry (i, k, b) at 10 (3 i + k) + b, f_i at 90 + i
-constexpr int kRowElems = 25;     // elements per pass-1 workgroup
-constexpr int kRowThreads = 128;  // 125 point lanes
-constexpr int kRecL = 92;         // LDS record stride in values (a 16-byte multiple)
-constexpr int kRowStage = 7;      // incidences a wave contracts at a time (63 of its lanes)
-constexpr int kDnL = 20;          // LDS stride of a node's gradient row (16 used; 20 keeps the rows
-                                  // of the ten nodes on different banks)
-constexpr int kStgL = 100;        // LDS stride of a staged row block (96 used; spreads the banks)
+// Pass 1 reduces over the points itself: a lane per point forms the point's
+// tangent and stress, then a lane per task (element, node a, row i, component
+// k) contracts the element's five points exactly as the gather does, giving
+// the ten entries K_e[3a+i][3b+k], b = 0..9, summed over the points (Sec.
+// 4.4.2, Eq. tangent_block), and its part P_ik dN_a,k of f_a,i (Eq.
+// fint_local).  Each (element, node) row block goes to the node's place in the
+// node-sorted incidence list, so that pass 2 reads the blocks of a node range
+// as one contiguous run, each block once, instead of re-reading per-point
+// records for every range that shares an element.
+constexpr int kRowChunk = 32;           // row i of a block: K entry (k, b) at 10 k + b, f_i at 30, one pad
+constexpr int kRowBlk = 3 * kRowChunk;  // block: rows i = 0, 1, 2 (float32: one cache line each)
+constexpr int kRowElems = 12;           // elements per pass-1 workgroup: one wave, 60 point lanes
+constexpr int kRowGroup = 4;            // elements a wave contracts at a time (60 lanes of two tasks each)
+constexpr int kLptTile = 25;            // elements per item of the persistent batch schedule (or 16)
+// undamped materials, float32
+constexpr int kSymElems = 25;           // elements per pass-1 workgroup
+constexpr int kSymThreads = 128;        // 125 point lanes
+constexpr int kRecL = 92;               // LDS record stride in values (a 16-byte multiple; ANCF rows)
+constexpr int kDnL = 20;                // LDS stride of a node's gradient row (16 used; 20 keeps the rows
+                                        // of the ten nodes on different banks)
+constexpr int kStgL = 100;              // LDS stride of a staged row block (96 used; spreads the banks)
 
 // Phase B of the element rows for a symmetric tangent (undamped materials):
 // K_e^(ki)[b, a] = K_e^(ik)[a, b], so only the slots i <= k are contracted.
@@ -804,7 +808,7 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
     dna[4 * u + 2] = x[2];
     dna[4 * u + 3] = x[3];
   }
-  for (int le = wave; le < ne; le += kRowThreads / 64) {  // uniform per wave
+  for (int le = wave; le < ne; le += kSymThreads / 64) {  // uniform per wave
     const int32_t my_pos = lane < NEN ? incpos[(e0 + le) * NEN + lane] : 0;
     float acc[NEN], fd = 0.0f, ft = 0.0f;
 #pragma unroll
@@ -826,7 +830,7 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
     });
     wave_sync();  // the previous element's blocks have left the buffer
     if (lane < 6 * NEN) {
-      float* own = stg + an * kStgL + kSlot * (3 * i + k);
+      float* own = stg + an * kStgL + kRowChunk * i + kSlot * k;
 #pragma unroll
       for (int u = 0; u < NEN / 2; ++u) {
         f32x2 v;
@@ -836,7 +840,7 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
       }
       if (i < k) {
 #pragma unroll
-        for (int b = 0; b < NEN; ++b) stg[b * kStgL + kSlot * (3 * k + i) + an] = acc[b];
+        for (int b = 0; b < NEN; ++b) stg[b * kStgL + kRowChunk * k + kSlot * i + an] = acc[b];
       }
     }
     // f_a,0 = (0,0) + (0,1) + (0,2);  f_a,1 = (1,0) + (1,1) + (1,2);  f_a,2 = (2,0) + (2,1) + (2,2),
@@ -847,8 +851,8 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
     const float d00 = __shfl(fd, l0, 64), d11 = __shfl(fd, l0 + 3, 64), d22 = __shfl(fd, l0 + 5, 64);
     if (lane < 6 * NEN && us < 3) {
       const float fv = us == 0 ? (d00 + d01) + d02 : us == 1 ? (t01 + d11) + d12 : (t02 + t12) + d22;
-      stg[an * kStgL + 9 * kSlot + us] = fv;
-      stg[an * kStgL + 9 * kSlot + 3 + us] = 0.0f;
+      stg[an * kStgL + kRowChunk * us + 3 * kSlot] = fv;
+      stg[an * kStgL + kRowChunk * us + 3 * kSlot + 1] = 0.0f;
     }
     wave_sync();
 #pragma unroll
@@ -856,34 +860,33 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
       const int pc = lane + 64 * u, bl = pc / (kRowBlk / 4), pi = pc - bl * (kRowBlk / 4);
       const int32_t pb = __shfl(my_pos, bl < NEN ? bl : 0, 64);
       if (bl < NEN)
-        *reinterpret_cast<f32x4*>(rows + (int64_t)pb * kRowBlk + 4 * pi) =
-            *reinterpret_cast<const f32x4*>(stg + bl * kStgL + 4 * pi);
+        __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(stg + bl * kStgL + 4 * pi),
+                                    reinterpret_cast<f32x4*>(rows + (int64_t)pb * kRowBlk + 4 * pi));
     }
   }
 }
 
-template <class Rule, int EB = kRowElems, bool SYM = false>
-__device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
-                                               float* __restrict__ rows, int64_t blk) {
+// Symmetric tangent (undamped materials, float32): 25 elements in two waves,
+// the 64-value records of all their points in LDS.  480,000 elements: 0.580 ms
+// with plain stores, 0.466 with non-temporal ones.
+template <class Rule>
+__global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, const int32_t* __restrict__ incpos,
+                                                              float* __restrict__ rows) {
   static_assert(Rule::MC == 1 && Rule::NEN == 10, "element rows are built for T10");
-  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN;
-  constexpr int REC = SYM ? kRecS : kRecL;  // LDS record stride
-  static_assert(EB * NQ <= kRowThreads, "a lane per point");
-  static_assert(kRowThreads % 64 == 0 && 9 * kRowStage <= 64, "a wave stages whole incidences");
-  __shared__ __align__(16) float rec[EB * NQ * REC];
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kSymElems;
+  static_assert(EB * NQ <= kSymThreads, "a lane per point");
+  __shared__ __align__(16) float rec[EB * NQ * kRecS];
   __shared__ __align__(16) float dn[NEN * kDnL];  // parent gradients of every node at every point
-  __shared__ int32_t pos[SYM ? 1 : EB * NEN];     // incidence position of every (element, node)
-  __shared__ __align__(16) float stage_buf[(kRowThreads / 64) * (SYM ? NEN : kRowStage) * kStgL];  // per-wave blocks
+  __shared__ __align__(16) float stage_buf[(kSymThreads / 64) * NEN * kStgL];  // per-wave blocks
   static_assert(EB * nodal_doubles<Rule>() * sizeof(double) <= sizeof(rec), "nodal values fit the record area");
   const int tid = threadIdx.x;
-  const int64_t e0 = blk * EB;
+  const int64_t e0 = (int64_t)blockIdx.x * EB;
   const int ne = (int)(a.n_elem - e0 < EB ? a.n_elem - e0 : EB);
-  // 1. nodal values, the tables of the tasks, then each point's kinematics
+  // 1. nodal values, the gradient table, then each point's kinematics
   double* nod = reinterpret_cast<double*>(rec);
   gather_nodal<Rule>(a, e0, ne, nod);
-  if constexpr (!SYM)
-    for (int idx = tid; idx < ne * NEN; idx += kRowThreads) pos[idx] = incpos[e0 * NPN + idx];
-  for (int idx = tid; idx < NEN * 16; idx += kRowThreads) dn[kDnL * (idx / 16) + idx % 16] = Rule::template rows<float>(idx / 16)[idx % 16];
+  for (int idx = tid; idx < NEN * 16; idx += kSymThreads)
+    dn[kDnL * (idx / 16) + idx % 16] = Rule::template rows<float>(idx / 16)[idx % 16];
   __syncthreads();
   double* terms = nod + EB * NEN * 6;
   t10_element_terms<2, 6>(nod, ne, terms);
@@ -894,108 +897,183 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
   double Jinv[9], det, Hd[9], Fd[9];
   tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e0 + el, q, Jinv, det, Hd, Fd);
   __syncthreads();  // the nodal values are consumed: the LDS holds the records from here on
-  // 2. the point's record (slot layout of the records above) into LDS
+  // 2. the point's record into LDS, then the contraction
   PointOut<float> o;
   const unsigned fl = point_update<float, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
   if (act && fl) atomicOr(a.flags, fl);
   HatOut<float> h;
   to_parent<float, true>(o, Jinv, h);
   if (act) {
-    float* r = rec + pl * REC;
-    sfor<0, REC / 4>([&](auto jc) __attribute__((always_inline)) {
+    float* r = rec + pl * kRecS;
+    sfor<0, kRecS / 4>([&](auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value;
       f32x4 v;
       sfor<0, 4>([&](auto xc) __attribute__((always_inline)) {
         constexpr int x = decltype(xc)::value;
-        if constexpr (SYM) v[x] = record_value_sym<4 * j + x>(h);
-        else v[x] = record_value<4 * j + x>(h);
+        v[x] = record_value_sym<4 * j + x>(h);
       });
       *reinterpret_cast<f32x4*>(r + 4 * j) = v;
     });
   }
   __syncthreads();
-  if constexpr (SYM) {
-    elem_rows_sym_contract<Rule, EB>(incpos, rows, e0, ne, rec, dn, stage_buf);
-  } else {
-  // 3. a lane per task: each wave takes 2 x 7 whole incidences at a time (63
-  //    lanes, two tasks of the same slot each), contracts the element's
-  //    points, and stages the row blocks, 7 at a time, in its LDS buffer; f_a,i
-  //    is the sum of the three component lanes' parts, taken in a fixed order.
-  //    The blocks leave with 16-byte stores of consecutive lanes (whole cache
-  //    lines).
-  const int lane = tid & 63, wave = tid >> 6;
-  float* stg = stage_buf + wave * kRowStage * kStgL;
-  const int li = lane / 9, sl = lane - 9 * li, i = sl / 3, k = sl - 3 * i;  // lane 63: li = 7, idle
-  const int n_inc = ne * NEN;
-  constexpr int kGroup = 2 * kRowStage;  // incidences per wave and iteration
-  for (int c0 = kGroup * wave; c0 < n_inc; c0 += kGroup * (kRowThreads / 64)) {  // uniform per wave
-    float acc[2][NEN], facc[2];
-    sfor<0, 2>([&](auto hc) __attribute__((always_inline)) {
-      constexpr int hh = decltype(hc)::value;
-      const int ci = c0 + kRowStage * hh + li;
-      const int cc = (li < kRowStage && ci < n_inc) ? ci : c0;  // idle lanes repeat a live incidence
-      const int le = cc / NEN, an = cc - NEN * le;
-      float dna[16];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const f32x4 x = reinterpret_cast<const f32x4*>(dn + kDnL * an)[u];
-        dna[4 * u] = x[0];
-        dna[4 * u + 1] = x[1];
-        dna[4 * u + 2] = x[2];
-        dna[4 * u + 3] = x[3];
-      }
-#pragma unroll
-      for (int b = 0; b < NEN; ++b) acc[hh][b] = 0.0f;
-      facc[hh] = 0.0f;
-      const float* base = rec + le * NQ * REC;
-      const SlotRef sr = slot_ref<SYM>(i, k);
-      sfor<0, NQ>([&](auto qc) __attribute__((always_inline)) {
-        constexpr int qq = decltype(qc)::value;
-        Slot<float, true> sv;
-        read_slot<SYM>(base + qq * REC, sr, sv.v);
-        contract_point<Rule, float, true, true, qq, NEN>(sv, dna[3 * qq], dna[3 * qq + 1], dna[3 * qq + 2], k,
-                                                         acc[hh], facc[hh]);
-      });
-    });
-    sfor<0, 2>([&](auto hc) __attribute__((always_inline)) {
-      constexpr int hh = decltype(hc)::value;
-      const int g0 = c0 + kRowStage * hh;  // first incidence of this half
-      const float f1 = __shfl_down(facc[hh], 1, 64), f2 = __shfl_down(facc[hh], 2, 64);
-      wave_sync();  // the previous blocks have left the buffer
-      if (li < kRowStage) {
-        float* blk = stg + li * kStgL;
-#pragma unroll
-        for (int u = 0; u < NEN / 2; ++u) {
-          f32x2 v;
-          v[0] = acc[hh][2 * u];
-          v[1] = acc[hh][2 * u + 1];
-          *reinterpret_cast<f32x2*>(blk + kSlot * sl + 2 * u) = v;
-        }
-        if (k == 0) blk[9 * kSlot + i] = (facc[hh] + f1) + f2;
-        if (sl < 3) blk[9 * kSlot + 3 + sl] = 0.0f;
-      }
-      wave_sync();
-      const int nb = n_inc - g0 < kRowStage ? n_inc - g0 : kRowStage;  // blocks of this half (may be <= 0)
-#pragma unroll
-      for (int u = 0; u < (kRowStage * kRowBlk / 4 + 63) / 64; ++u) {
-        const int pc = lane + 64 * u, bl = pc / (kRowBlk / 4), pi = pc - bl * (kRowBlk / 4);
-        if (bl < nb)
-          *reinterpret_cast<f32x4*>(rows + (int64_t)pos[g0 + bl] * kRowBlk + 4 * pi) =
-              *reinterpret_cast<const f32x4*>(stg + bl * kStgL + 4 * pi);
-      }
-    });
-  }
-  }
+  elem_rows_sym_contract<Rule, EB>(incpos, rows, e0, ne, rec, dn, stage_buf);
 }
 
-template <class Rule, bool SYM>
-__global__ __launch_bounds__(kRowThreads) void k_elem_rows(AsmArgs a, const int32_t* incpos, float* rows) {
-  elem_rows_tile<Rule, kRowElems, SYM>(a, incpos, rows, blockIdx.x);
+// The row blocks of elements e0 .. e0 + ne - 1 (ne <= kRowElems), one wave.
+// A point's factors (HatOut) stay in its lane's registers; the rows i = 0, 1,
+// 2 of the element matrices are formed one after the other, so that LDS holds
+// only the three slots (i, k) of every point at a time (30 values instead of
+// 90).  For each row the wave takes four elements at a time, a lane per
+// (element, component k, nodes a and a + 5): the lane reads a slot once for
+// both nodes, contracts the five points, and the 40 rows leave through LDS
+// with 16-byte stores of consecutive lanes (whole cache lines).  A single wave
+// needs no barrier, and waves in different phases share a SIMD.
+// The stores are non-temporal: no line is written twice or read by this pass,
+// and through the L2 (4 MB against the 13 MB that one XCD's waves have in
+// flight) they left in an order that HBM took at 3.3 TB/s.
+// Bound by instruction issue (5,000 a wave, 66 % of it) and by the 1.84 GB of
+// stores.  480,000 elements, float32: 0.672 ms with two-wave workgroups of 25
+// elements and whole records in LDS (53 KB, 1.5 waves per SIMD), 0.565 row by
+// row in single waves, 0.465 with non-temporal stores; without any store it
+// takes 0.375.  One node per lane, held to three waves per SIMD, is as fast.
+template <class Rule, typename R>
+__device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
+                                               R* __restrict__ rows, int64_t e0, int ne) {
+  static_assert(Rule::MC == 1 && Rule::NEN == 10 && 3 * kSlot <= kRowChunk, "element rows are built for T10");
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kRowElems, HN = NEN / 2;
+  static_assert(EB * NQ <= 64 && 3 * HN * kRowGroup <= 64, "a lane per point and per pair of tasks");
+  using V = typename Vec4<R>::type;
+  typedef R R2 __attribute__((ext_vector_type(2)));
+  constexpr int PER = (int)(sizeof(V) / sizeof(R));         // values per 16-byte piece
+  constexpr int RS = 3 * kSlot + (sizeof(R) == 4 ? 6 : 4);  // stride of a point's slots: on different banks
+  constexpr int SS = kRowChunk + 2;                         // stride of a staged row: the slots on different banks
+  constexpr int DL = 16 + PER;                              // stride of a node's gradient row
+  constexpr size_t NOD = (size_t)EB * nodal_doubles<Rule>() * sizeof(double), REC = (size_t)EB * NQ * RS * sizeof(R);
+  __shared__ __align__(16) unsigned char smem[NOD > REC ? NOD : REC];
+  __shared__ __align__(16) R stg[kRowGroup * NEN * SS];
+  __shared__ __align__(16) R dn[NEN * DL];  // parent gradients of every node at every point
+  __shared__ int32_t pos[EB * NEN];         // incidence position of every (element, node)
+  const int lane = threadIdx.x;
+  // 1. nodal values, the tables of the tasks, then each point's kinematics
+  double* nod = reinterpret_cast<double*>(smem);
+  gather_nodal<Rule>(a, e0, ne, nod);
+  for (int idx = lane; idx < ne * NEN; idx += 64) pos[idx] = incpos[e0 * NEN + idx];
+  for (int idx = lane; idx < NEN * 16; idx += 64) dn[DL * (idx / 16) + idx % 16] = Rule::template rows<R>(idx / 16)[idx % 16];
+  wave_sync();
+  double* terms = nod + EB * NEN * 6;
+  t10_element_terms<2, 6>(nod, ne, terms);
+  wave_sync();
+  const bool act = lane < ne * NQ;
+  const int pl = act ? lane : 0;  // idle lanes evaluate point 0 and store nothing
+  const int el = pl / NQ, q = pl - el * NQ;
+  double Jinv[9], det, Hd[9], Fd[9];
+  tile_kinematics<Rule>(a, nod + 6 * NEN * el, terms + 2 * kT10Terms * el, e0 + el, q, Jinv, det, Hd, Fd);
+  PointOut<R> o;
+  const unsigned fl = point_update<R, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
+  if (act && fl) atomicOr(a.flags, fl);
+  HatOut<R> h;
+  to_parent<R, true, FuseT10Full>(o, Jinv, h);
+  // 2. row by row
+  R* rec = reinterpret_cast<R*>(smem);  // the nodal values are consumed
+  const int eg = lane / (3 * HN), an = (lane - 3 * HN * eg) / 3, k = lane % 3;  // lanes 60 .. 63: eg = 4, idle
+  sfor<0, 3>([&](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    wave_sync();  // the previous row's slots are consumed
+    if (act) {
+      R* r = rec + pl * RS;
+      sfor<0, (3 * kSlot + PER - 1) / PER>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value;
+        V v;
+        sfor<0, PER>([&](auto xc) __attribute__((always_inline)) {
+          constexpr int w = PER * j + decltype(xc)::value;
+          if constexpr (w < 3 * kSlot) v[decltype(xc)::value] = record_value<3 * kSlot * i + w, FuseT10Full>(h);
+          else v[decltype(xc)::value] = R(0);
+        });
+        *reinterpret_cast<V*>(r + PER * j) = v;
+      });
+    }
+    wave_sync();
+#pragma unroll 1
+    for (int g0 = 0; g0 < ne; g0 += kRowGroup) {
+      const int ng = ne - g0 < kRowGroup ? ne - g0 : kRowGroup;  // elements of this group
+      const int le = g0 + (eg < ng ? eg : 0);                    // idle lanes repeat a live element
+      R dna[2][16], acc[2][NEN], facc[2];
+#pragma unroll
+      for (int z = 0; z < 2; ++z) {
+#pragma unroll
+        for (int u = 0; u < 16 / PER; ++u) {
+          const V x = reinterpret_cast<const V*>(dn + DL * (an + HN * z))[u];
+#pragma unroll
+          for (int t = 0; t < PER; ++t) dna[z][PER * u + t] = x[t];
+        }
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) acc[z][b] = R(0);
+        facc[z] = R(0);
+      }
+      const R* base = rec + le * NQ * RS + kSlot * k;
+      sfor<0, NQ>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int qq = decltype(qc)::value;
+        Slot<R, true> sv;
+        load_slot<R, true>(base + qq * RS, sv);
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+          contract_point<Rule, R, true, true, qq, NEN>(sv, dna[z][3 * qq], dna[z][3 * qq + 1], dna[z][3 * qq + 2], k,
+                                                       acc[z], facc[z]);
+      });
+      R f1[2], f2[2];
+#pragma unroll
+      for (int z = 0; z < 2; ++z) {
+        f1[z] = __shfl_down(facc[z], 1, 64);
+        f2[z] = __shfl_down(facc[z], 2, 64);
+      }
+      wave_sync();  // the previous rows have left the buffer
+      if (eg < ng) {
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          R* row = stg + (NEN * eg + an + HN * z) * SS;
+#pragma unroll
+          for (int u = 0; u < NEN / 2; ++u) {
+            R2 v;
+            v[0] = acc[z][2 * u];
+            v[1] = acc[z][2 * u + 1];
+            *reinterpret_cast<R2*>(row + kSlot * k + 2 * u) = v;
+          }
+          if (k == 0) {
+            R2 v;
+            v[0] = (facc[z] + f1[z]) + f2[z];
+            v[1] = R(0);
+            *reinterpret_cast<R2*>(row + 3 * kSlot) = v;
+          }
+        }
+      }
+      wave_sync();
+      constexpr int NP = kRowChunk / PER;  // pieces per row
+#pragma unroll
+      for (int u = 0; u < (kRowGroup * NEN * NP + 63) / 64; ++u) {
+        const int pc = lane + 64 * u, bl = pc / NP, pi = pc - bl * NP;
+        if (bl < ng * NEN) {
+          const R2* src = reinterpret_cast<const R2*>(stg + bl * SS + PER * pi);
+          V v;
+#pragma unroll
+          for (int t = 0; t < PER; ++t) v[t] = src[t / 2][t % 2];
+          __builtin_nontemporal_store(
+              v, reinterpret_cast<V*>(rows + (int64_t)pos[g0 * NEN + bl] * kRowBlk + kRowChunk * i + PER * pi));
+        }
+      }
+    }
+  });
+}
+
+template <class Rule, typename R>
+__global__ __launch_bounds__(64, 2) void k_elem_rows(AsmArgs a, const int32_t* __restrict__ incpos,
+                                                    R* __restrict__ rows) {
+  const int64_t e0 = (int64_t)blockIdx.x * kRowElems;
+  elem_rows_tile<Rule, R>(a, incpos, rows, e0, (int)(a.n_elem - e0 < kRowElems ? a.n_elem - e0 : kRowElems));
 }
 
 // many bodies: every body starts on a workgroup of its own, found by bisection
 template <class Rule>
-__global__ __launch_bounds__(kRowThreads) void k_elem_rows_batch(BatchArgs b) {
+__global__ __launch_bounds__(64, 2) void k_elem_rows_batch(BatchArgs b) {
   const int64_t blk = blockIdx.x;
   int lo = 0, hi = b.n_bodies - 1;
   while (lo < hi) {
@@ -1004,15 +1082,17 @@ __global__ __launch_bounds__(kRowThreads) void k_elem_rows_batch(BatchArgs b) {
   }
   const BatchBody& B = b.bodies[lo];
   const AsmArgs a = body_args(b, B, lo);
-  elem_rows_tile<Rule>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, blk - B.rblock_off);
+  const int64_t e0 = (blk - B.rblock_off) * kRowElems;
+  elem_rows_tile<Rule, float>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, e0,
+                              (int)(a.n_elem - e0 < kRowElems ? a.n_elem - e0 : kRowElems));
 }
 
 // Persistent form of the batch (the LPT schedule): a grid sized to what the
 // GPU holds at once, whose workgroups take (body, tile) items from a counter
 // in a list ordered longest first (full tiles of the largest bodies first,
-// partial tiles last), EB elements per tile.
+// partial tiles last), EB elements per tile, which the wave takes in equal parts.
 template <class Rule, int EB>
-__global__ __launch_bounds__(kRowThreads) void k_elem_rows_batch_lpt(BatchArgs b, const int2* __restrict__ items,
+__global__ __launch_bounds__(64, 2) void k_elem_rows_batch_lpt(BatchArgs b, const int2* __restrict__ items,
                                                                     int n_items, unsigned* __restrict__ counter) {
   __shared__ int item;
   for (;;) {
@@ -1024,7 +1104,14 @@ __global__ __launch_bounds__(kRowThreads) void k_elem_rows_batch_lpt(BatchArgs b
     const int2 t = items[it];
     const BatchBody& B = b.bodies[t.x];
     const AsmArgs a = body_args(b, B, t.x);
-    elem_rows_tile<Rule, EB>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, t.y);
+    constexpr int parts = (EB + kRowElems - 1) / kRowElems, step = (EB + parts - 1) / parts;
+    const int64_t end = (int64_t)(t.y + 1) * EB < a.n_elem ? (int64_t)(t.y + 1) * EB : a.n_elem;
+#pragma unroll 1
+    for (int64_t e0 = (int64_t)t.y * EB; e0 < end; e0 += step) {
+      wave_sync();  // the previous part's LDS is consumed
+      elem_rows_tile<Rule, float>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, e0,
+                                  (int)(end - e0 < step ? end - e0 : step));
+    }
   }
 }
 
@@ -1034,8 +1121,8 @@ __global__ void k_reset_counters(unsigned* counters) {
 
 // Pass 2 over the row blocks: a lane per (incidence, row i, component k) task
 // of the range loads its ten K entries (three aligned 16-byte pieces of the
-// block, shifted by 2 values for odd slots) and adds them into the range's
-// LDS segment at row + 3 rank_b + k; lanes with k = 0 add the force entry.
+// row, shifted by 2 values for k = 1) and adds them into the range's LDS
+// segment at row + 3 rank_b + k; the pieces of k = 2 end with the force entry.
 template <bool WANT_F, bool WANT_K, bool ACCUM>
 __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int32_t I1, unsigned char* smem,
                                             int32_t* pre, int32_t* rowo) {
@@ -1069,10 +1156,10 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int
     const int rl = 3 * incn[jl] + i;
     if constexpr (WANT_K) {
       // 16-byte units with 32-bit offsets (checked on the host)
-      const uint32_t p0 = j * (uint32_t)(kRowBlk / 4) + (uint32_t)((kSlot * sl) >> 2);
+      const uint32_t p0 = j * (uint32_t)(kRowBlk / 4) + (uint32_t)((kRowChunk * i + kSlot * k) >> 2);
       const f32x4 w[3] = {blkv[p0], blkv[p0 + 1], blkv[p0 + 2]};
       const u32x4 rw = *reinterpret_cast<const u32x4*>(g.rank + (size_t)j * 16);
-      const bool odd = sl & 1;
+      const bool odd = k == 1;
       double* dstp = lds + rowo[rl] + k;
 #pragma unroll
       for (int b = 0; b < 10; ++b) {
@@ -1080,9 +1167,11 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int
         const int rank_b = (int)((rw[b >> 2] >> (8 * (b & 3))) & 255u);
         atomicAdd(dstp + 3 * rank_b, (double)(odd ? hi : lo));
       }
+      if constexpr (WANT_F)
+        if (k == 2) atomicAdd(lf + rl, (double)w[2][2]);
+    } else {
+      if (k == 0) atomicAdd(lf + rl, (double)blk[(size_t)j * kRowBlk + kRowChunk * i + 3 * kSlot]);
     }
-    if constexpr (WANT_F)
-      if (k == 0) atomicAdd(lf + rl, (double)blk[(size_t)j * kRowBlk + 9 * kSlot + i]);
   }
   __syncthreads();
   if constexpr (WANT_K) write_segment<ACCUM>(g, row0, nrow, nseg, seg0, lds, rowo);
@@ -1379,8 +1468,9 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
   PointOut<float> o;
   const unsigned fl = point_update<float, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
   if (act && fl) atomicOr(a.flags, fl);
+  using FO = std::conditional_t<!SYM && NEN == 8, FuseBeamFull, FuseOther>;
   HatOut<float> h;
-  to_parent<float, true>(o, Jinv, h);
+  to_parent<float, true, FO>(o, Jinv, h);
   float* rec = reinterpret_cast<float*>(smem);
   if (act) {
     float* r = rec + pl * RS;
@@ -1390,7 +1480,7 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
       sfor<0, 4>([&](auto xc) __attribute__((always_inline)) {
         constexpr int x = decltype(xc)::value;
         if constexpr (SYM) v[x] = record_value_sym<4 * j + x>(h);
-        else v[x] = record_value<4 * j + x>(h);
+        else v[x] = record_value<4 * j + x, FO>(h);
       });
       *reinterpret_cast<f32x4*>(r + 4 * j) = v;
     });
@@ -2010,7 +2100,7 @@ size_t stage_bytes(const Mesh& m, bool want_k) {
 }
 
 size_t row_block_bytes() { return kRowBlk * sizeof(float); }
-int row_elems() { return kRowElems; }
+int lpt_tile_elems() { return kLptTile; }
 
 size_t row_block_bytes_for(int elem_type, int gl0) {
   if (elem_type == TLFEA_T10) return row_block_bytes();
@@ -2033,10 +2123,10 @@ int batch_lpt_occupancy(int tile_elems, int waves, size_t lds_all, int* tiles_pe
   int nt = 0, nr = 0;
   if (tile_elems == 16)
     TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, 16>), kRowThreads, 0));
+        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, 16>), 64, 0));
   else
     TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, kRowElems>), kRowThreads, 0));
+        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, kLptTile>), 64, 0));
   if (int rc = allow_lds(k_gather_rows_batch_lpt, lds_all)) return rc;
   TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
       &nr, reinterpret_cast<const void*>(k_gather_rows_batch_lpt), 64 * waves, lds_all));
@@ -2064,15 +2154,17 @@ int launch_points(const Mesh& m, const AsmArgs& a, bool want_k, hipStream_t s) {
     return launch_rows_mc_points<RuleAncf<4, 4, 3>>(m, a, s);
   }
   if (use_rows(m, want_k)) {
-    const int64_t blocks = (m.n_elem + kRowElems - 1) / kRowElems;
+    const bool sym = sym_records(m);
+    const int64_t eb = sym ? kSymElems : kRowElems, blocks = (m.n_elem + eb - 1) / eb;
     if (blocks > INT32_MAX) return TLFEA_ERR_TOO_LARGE;
-    if (blocks > 0)
-      if (sym_records(m))
-        hipLaunchKernelGGL((k_elem_rows<RuleT10, true>), dim3((unsigned)blocks), dim3(kRowThreads), 0, s, a,
-                           m.d_incpos, (float*)m.d_stage);
+    if (blocks > 0) {
+      if (sym)
+        hipLaunchKernelGGL(k_elem_rows_sym<RuleT10>, dim3((unsigned)blocks), dim3(kSymThreads), 0, s, a, m.d_incpos,
+                           (float*)m.d_stage);
       else
-        hipLaunchKernelGGL((k_elem_rows<RuleT10, false>), dim3((unsigned)blocks), dim3(kRowThreads), 0, s, a,
-                           m.d_incpos, (float*)m.d_stage);
+        hipLaunchKernelGGL((k_elem_rows<RuleT10, float>), dim3((unsigned)blocks), dim3(64), 0, s, a, m.d_incpos,
+                           (float*)m.d_stage);
+    }
     TLFEA_HIP_CHECK(hipGetLastError());
     return TLFEA_OK;
   }
@@ -2201,10 +2293,10 @@ int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, 
     hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, sc.counters);
     if (sc.n_tiles > 0) {
       if (sc.tile_elems == 16)
-        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, 16>), dim3(sc.grid_tiles), dim3(kRowThreads), 0, s, b,
+        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, 16>), dim3(sc.grid_tiles), dim3(64), 0, s, b,
                            sc.tiles, sc.n_tiles, sc.counters);
       else
-        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, kRowElems>), dim3(sc.grid_tiles), dim3(kRowThreads), 0, s,
+        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, kLptTile>), dim3(sc.grid_tiles), dim3(64), 0, s,
                            b, sc.tiles, sc.n_tiles, sc.counters);
     }
     TLFEA_HIP_CHECK(hipGetLastError());
@@ -2222,7 +2314,7 @@ int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, 
   }
   if (b.rows) {
     if (b.n_rblocks > 0)
-      hipLaunchKernelGGL(k_elem_rows_batch<RuleT10>, dim3((unsigned)b.n_rblocks), dim3(kRowThreads), 0, s, b);
+      hipLaunchKernelGGL(k_elem_rows_batch<RuleT10>, dim3((unsigned)b.n_rblocks), dim3(64), 0, s, b);
     TLFEA_HIP_CHECK(hipGetLastError());
     const size_t lds_all = lds + b.inc_cap;
     if (int rc = allow_lds(k_gather_rows_batch, lds_all)) return rc;

@@ -95,7 +95,7 @@ static int upload(T*& d, size_t& cap, const std::vector<T>& h) {
 // many workgroups as the GPU holds at once.
 static int batch_plan_lpt(tlfea_batch_s* b, int tile_elems) {
   if (!b->rows || b->elem_type != TLFEA_T10) return TLFEA_ERR_UNSUPPORTED;
-  if (tile_elems != 16 && tile_elems != tlfea::row_elems()) return TLFEA_ERR_INVALID;
+  if (tile_elems != 16 && tile_elems != tlfea::lpt_tile_elems()) return TLFEA_ERR_INVALID;
   struct Tile {
     int64_t work, body_size;
     int body, tile;
@@ -483,12 +483,12 @@ TLFEA_API int tlfea_batch_autotune(tlfea_batch_t b, const double* d_q, const dou
   struct Cand {
     int persistent, tile_elems;
   };
-  std::vector<Cand> cands{{0, tlfea::row_elems()}};
+  std::vector<Cand> cands{{0, tlfea::lpt_tile_elems()}};
   if (b->rows && b->elem_type == TLFEA_T10) {
-    cands.push_back({1, tlfea::row_elems()});
+    cands.push_back({1, tlfea::lpt_tile_elems()});
     cands.push_back({1, 16});
   }
-  const Cand cur{b->sched.persistent, b->sched.persistent ? b->sched.tile_elems : tlfea::row_elems()};
+  const Cand cur{b->sched.persistent, b->sched.persistent ? b->sched.tile_elems : tlfea::lpt_tile_elems()};
   const tlfea::GatherTuning cur_shape = b->tune;
   TunedChoice best, at_cur;
   float best_ms = -1.0f, cur_ms = -1.0f;

@@ -54,6 +54,13 @@ __device__ __forceinline__ double jm1_of(const double* H) {
   return tr + 0.5 * (tr * tr - trH2) + det3d(H);
 }
 
+// x0^2 + x1^2 + x2^2, every product and sum rounded (spelled out: see sum3 below)
+template <typename R>
+__device__ __forceinline__ R sum_squares(R x0, R x1, R x2) {
+#pragma clang fp contract(off)
+  return (x0 * x0 + x1 * x1) + x2 * x2;
+}
+
 // Output of the constitutive update: P (row-major) and the factors of A,
 // both already multiplied by the quadrature volume dV.
 template <typename R>
@@ -107,7 +114,8 @@ __device__ __forceinline__ unsigned point_update(const MatParams& mp, const doub
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j)
-        B[3 * i + j] = F[3 * i] * F[3 * j] + F[3 * i + 1] * F[3 * j + 1] + F[3 * i + 2] * F[3 * j + 2];
+        B[3 * i + j] = i == j ? sum_squares(F[3 * i], F[3 * i + 1], F[3 * i + 2])
+                              : F[3 * i] * F[3 * j] + F[3 * i + 1] * F[3 * j + 1] + F[3 * i + 2] * F[3 * j + 2];
   }
 
   double jm1 = jm1_of(Hd);
@@ -182,7 +190,8 @@ __device__ __forceinline__ unsigned point_update(const MatParams& mp, const doub
       for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j)
-          C[3 * i + j] = F[i] * F[j] + F[3 + i] * F[3 + j] + F[6 + i] * F[6 + j];
+          C[3 * i + j] = i == j ? sum_squares(F[i], F[3 + i], F[6 + i])
+                                : F[i] * F[j] + F[3 + i] * F[3 + j] + F[6 + i] * F[6 + j];
       R FC[9];
 #pragma unroll
       for (int i = 0; i < 3; ++i)
@@ -514,50 +523,78 @@ struct HatOut {
   bool mr;
 };
 
-template <typename R>
+// Which of two products of a sum is fused into a multiply-add decides the last
+// bit of a float32 result, and left to the compiler it follows the code around
+// it.  The sums below are therefore spelled out, with the orders as template
+// arguments, so that a kernel keeps its results when its schedule changes.
+//   sum3<SW>: x0 y0 + x1 y1 + x2 y2, the rounded product the first (SW) or the second.
+//   FuseOrder: SW of the rows 0 and 1 of What, of its row 2, of Yhat and of Uhat;
+//   FY: F_in Y_km is the fused product of a tangent entry's first pair.
+template <bool SW, typename R>
+__device__ __forceinline__ R sum3(R x0, R y0, R x1, R y1, R x2, R y2) {
+  if constexpr (SW) return fma(x2, y2, fma(x1, y1, x0 * y0));
+  else return fma(x2, y2, fma(x0, y0, x1 * y1));
+}
+template <bool W01_, bool W2_, bool Y_, bool U_, bool FY_>
+struct FuseOrder {
+  static constexpr bool W01 = W01_, W2 = W2_, Y = Y_, U = U_, FY = FY_;
+};
+using FuseT10Full = FuseOrder<true, false, false, false, false>;  // element rows of T10, all nine slots
+using FuseBeamFull = FuseOrder<true, true, true, false, true>;    // of the beam, all nine slots
+using FuseOther = FuseOrder<true, true, true, true, true>;        // of the shells, and the symmetric layouts
+
+template <bool SW0, bool SW2, typename R>
 __device__ __forceinline__ void rows_times_jinvT(const R* X, const R* Ji, R* out) {
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
+  for (int m = 0; m < 3; ++m) {
 #pragma unroll
-    for (int m = 0; m < 3; ++m) out[3 * i + m] = X[3 * i] * Ji[3 * m] + X[3 * i + 1] * Ji[3 * m + 1] + X[3 * i + 2] * Ji[3 * m + 2];
+    for (int i = 0; i < 2; ++i)
+      out[3 * i + m] = sum3<SW0>(X[3 * i], Ji[3 * m], X[3 * i + 1], Ji[3 * m + 1], X[3 * i + 2], Ji[3 * m + 2]);
+    out[6 + m] = sum3<SW2>(X[6], Ji[3 * m], X[7], Ji[3 * m + 1], X[8], Ji[3 * m + 2]);
+  }
 }
 
-template <typename R, bool WANT_A>
+template <typename R, bool WANT_A, class FO = FuseOther>
 __device__ __forceinline__ void to_parent(const PointOut<R>& o, const double* Jinv64, HatOut<R>& h) {
   R Ji[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) Ji[t] = (R)Jinv64[t];
-  rows_times_jinvT(o.P, Ji, h.P);
+  rows_times_jinvT<false, false>(o.P, Ji, h.P);
   if (!WANT_A) return;
   h.mr = o.mr;
   h.cgx = o.cgx;
-  rows_times_jinvT(o.F, Ji, h.F);
-  rows_times_jinvT(o.W, Ji, h.W);
-  rows_times_jinvT(o.Y, Ji, h.Y);
+  rows_times_jinvT<false, false>(o.F, Ji, h.F);
+  rows_times_jinvT<FO::W01, FO::W2>(o.W, Ji, h.W);
+  rows_times_jinvT<FO::Y, FO::Y>(o.Y, Ji, h.Y);
   R T[9];
-  rows_times_jinvT(o.M, Ji, T);  // M Jinv^T, then Jinv (M Jinv^T)
+  rows_times_jinvT<true, true>(o.M, Ji, T);  // M Jinv^T, then Jinv (M Jinv^T)
 #pragma unroll
   for (int m = 0; m < 3; ++m)
 #pragma unroll
     for (int n = 0; n < 3; ++n) {
-      h.M[3 * m + n] = Ji[3 * m] * T[n] + Ji[3 * m + 1] * T[3 + n] + Ji[3 * m + 2] * T[6 + n];
-      h.C[3 * m + n] = Ji[3 * m] * Ji[3 * n] + Ji[3 * m + 1] * Ji[3 * n + 1] + Ji[3 * m + 2] * Ji[3 * n + 2];
+      h.M[3 * m + n] = sum3<true>(Ji[3 * m], T[n], Ji[3 * m + 1], T[3 + n], Ji[3 * m + 2], T[6 + n]);
+      h.C[3 * m + n] = sum3<false>(Ji[3 * m], Ji[3 * n], Ji[3 * m + 1], Ji[3 * n + 1], Ji[3 * m + 2], Ji[3 * n + 2]);
     }
 #pragma unroll
   for (int t = 0; t < 9; ++t) h.N[t] = o.N[t];
   if (o.mr) {
-    rows_times_jinvT(o.U, Ji, h.U);
-    rows_times_jinvT(o.V, Ji, h.V);
-    rows_times_jinvT(o.G, Ji, h.G);
+    rows_times_jinvT<FO::U, FO::U>(o.U, Ji, h.U);
+    rows_times_jinvT<false, false>(o.V, Ji, h.V);
+    rows_times_jinvT<false, false>(o.G, Ji, h.G);
   }
 }
 
-template <typename R>
+template <class FO = FuseOther, typename R>
 __device__ __forceinline__ R hat_entry(const HatOut<R>& h, int i, int m, int k, int n) {
-  R a = h.F[3 * i + m] * h.W[3 * k + n] + h.F[3 * i + n] * h.Y[3 * k + m] + h.N[3 * i + k] * h.C[3 * m + n];
+  R a = FO::FY ? fma(h.F[3 * i + n], h.Y[3 * k + m], h.F[3 * i + m] * h.W[3 * k + n])
+               : fma(h.F[3 * i + m], h.W[3 * k + n], h.F[3 * i + n] * h.Y[3 * k + m]);
+  a = fma(h.N[3 * i + k], h.C[3 * m + n], a);
   if (i == k) a += h.M[3 * m + n];
-  if (h.mr)
-    a += h.U[3 * i + m] * h.G[3 * k + n] + h.G[3 * i + m] * h.V[3 * k + n] + h.cgx * h.G[3 * i + n] * h.G[3 * k + m];
+  if (h.mr) {
+    const R u = 3 * k + n > 3 * i + m ? fma(h.G[3 * i + m], h.V[3 * k + n], h.U[3 * i + m] * h.G[3 * k + n])
+                                      : fma(h.U[3 * i + m], h.G[3 * k + n], h.G[3 * i + m] * h.V[3 * k + n]);
+    a += fma(h.cgx * h.G[3 * i + n], h.G[3 * k + m], u);
+  }
   return a;
 }
 

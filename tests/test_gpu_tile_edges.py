@@ -36,3 +36,20 @@ def test_t10_force_and_vjp_tiles(precision, n):
         assert rel_err(got.cpu().numpy(), ref)[0] <= TOL["fp64"]
     assert np.abs(gp.cpu().numpy() - refs[2]).max() <= 1e-12 * np.abs(refs[2]).max()
     m.close()
+
+
+# element rows: 12 elements a wave (damped), 25 a workgroup (undamped), four at a time
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 11, 12, 13, 24, 25, 26, 37])
+@pytest.mark.parametrize("damped", [True, False])
+def test_t10_row_tiles(damped, n):
+    print(f"[gpu] rows tile damped={damped} {n}", flush=True)
+    mat = W.Material(W.MOONEY_RIVLIN, (2e5, 5e4, 1e8), *((1e3, 7e2) if damped else ()))
+    wl = first_elements(W.t10_beam(3, 2, 2, 160 + n, "tile", material=mat), n)
+    m = make_mesh(wl, "mixed")
+    om = oracle.Mesh.of(wl.mesh)
+    f_ref, v_ref = oracle.assemble(om, oracle.material_of(mat), wl.q, wl.qdot, 1e-3, 1.0)
+    f, v = m.assemble(cuda(wl.q), cuda(wl.qdot), 1e-3, 1.0)
+    torch.cuda.synchronize()
+    assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
+    assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
+    m.close()
