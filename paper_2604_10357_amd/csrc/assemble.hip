@@ -767,8 +767,12 @@ __global__ __launch_bounds__(512) void k_gather_batch(BatchArgs b) {
 // records for every range that shares an element.
 constexpr int kRowChunk = 32;           // row i of a block: K entry (k, b) at 10 k + b, f_i at 30, one pad
 constexpr int kRowBlk = 3 * kRowChunk;  // block: rows i = 0, 1, 2 (float32: one cache line each)
-constexpr int kRowElems = 12;           // elements per pass-1 workgroup: one wave, 60 point lanes
-constexpr int kRowGroup = 4;            // elements a wave contracts at a time (60 lanes of two tasks each)
+constexpr int kRowElems = 12;           // most elements of a pass-1 workgroup: one wave, 60 point lanes
+// Waves per SIMD.  float64: the point's factors and the accumulators need 340
+// registers, and one wave with the overflow in accumulation registers beats
+// two that spill 81 to scratch (pass 1 of 480,000 elements 1.03 against 1.11 ms).
+template <typename R>
+constexpr int row_min_waves() { return sizeof(R) == 4 ? 2 : 1; }
 constexpr int kLptTile = 25;            // elements per item of the persistent batch schedule (or 16)
 // undamped materials, float32
 constexpr int kSymElems = 25;           // elements per pass-1 workgroup
@@ -870,7 +874,8 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
 // the 64-value records of all their points in LDS.  480,000 elements: 0.580 ms
 // with plain stores, 0.466 with non-temporal ones.
 template <class Rule>
-__global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, const int32_t* __restrict__ incpos,
+__global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, int tile,
+                                                              const int32_t* __restrict__ incpos,
                                                               float* __restrict__ rows) {
   static_assert(Rule::MC == 1 && Rule::NEN == 10, "element rows are built for T10");
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kSymElems;
@@ -880,8 +885,8 @@ __global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, const 
   __shared__ __align__(16) float stage_buf[(kSymThreads / 64) * NEN * kStgL];  // per-wave blocks
   static_assert(EB * nodal_doubles<Rule>() * sizeof(double) <= sizeof(rec), "nodal values fit the record area");
   const int tid = threadIdx.x;
-  const int64_t e0 = (int64_t)blockIdx.x * EB;
-  const int ne = (int)(a.n_elem - e0 < EB ? a.n_elem - e0 : EB);
+  const int64_t e0 = (int64_t)blockIdx.x * tile;
+  const int ne = (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile);
   // 1. nodal values, the gradient table, then each point's kinematics
   double* nod = reinterpret_cast<double*>(rec);
   gather_nodal<Rule>(a, e0, ne, nod);
@@ -940,17 +945,19 @@ template <class Rule, typename R>
 __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
                                                R* __restrict__ rows, int64_t e0, int ne) {
   static_assert(Rule::MC == 1 && Rule::NEN == 10 && 3 * kSlot <= kRowChunk, "element rows are built for T10");
-  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kRowElems, HN = NEN / 2;
-  static_assert(EB * NQ <= 64 && 3 * HN * kRowGroup <= 64, "a lane per point and per pair of tasks");
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kRowElems;
+  constexpr int Z = sizeof(R) == 4 ? 2 : 1, HN = NEN / Z;  // nodes per lane, lanes per (element, component)
+  constexpr int GRP = 64 / (3 * HN);                       // elements the wave contracts at a time
+  static_assert(EB * NQ <= 64, "a lane per point");
   using V = typename Vec4<R>::type;
   typedef R R2 __attribute__((ext_vector_type(2)));
   constexpr int PER = (int)(sizeof(V) / sizeof(R));         // values per 16-byte piece
-  constexpr int RS = 3 * kSlot + (sizeof(R) == 4 ? 6 : 4);  // stride of a point's slots: on different banks
+  constexpr int RS = 3 * kSlot + (sizeof(R) == 4 ? 6 : 0);  // stride of a point's slots: on different banks
   constexpr int SS = kRowChunk + 2;                         // stride of a staged row: the slots on different banks
   constexpr int DL = 16 + PER;                              // stride of a node's gradient row
   constexpr size_t NOD = (size_t)EB * nodal_doubles<Rule>() * sizeof(double), REC = (size_t)EB * NQ * RS * sizeof(R);
   __shared__ __align__(16) unsigned char smem[NOD > REC ? NOD : REC];
-  __shared__ __align__(16) R stg[kRowGroup * NEN * SS];
+  __shared__ __align__(16) R stg[GRP * NEN * SS];
   __shared__ __align__(16) R dn[NEN * DL];  // parent gradients of every node at every point
   __shared__ int32_t pos[EB * NEN];         // incidence position of every (element, node)
   const int lane = threadIdx.x;
@@ -975,7 +982,7 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
   to_parent<R, true, FuseT10Full>(o, Jinv, h);
   // 2. row by row
   R* rec = reinterpret_cast<R*>(smem);  // the nodal values are consumed
-  const int eg = lane / (3 * HN), an = (lane - 3 * HN * eg) / 3, k = lane % 3;  // lanes 60 .. 63: eg = 4, idle
+  const int eg = lane / (3 * HN), an = (lane - 3 * HN * eg) / 3, k = lane % 3;  // lanes 60 .. 63: eg = GRP, idle
   sfor<0, 3>([&](auto ic) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value;
     wave_sync();  // the previous row's slots are consumed
@@ -994,42 +1001,38 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
     }
     wave_sync();
 #pragma unroll 1
-    for (int g0 = 0; g0 < ne; g0 += kRowGroup) {
-      const int ng = ne - g0 < kRowGroup ? ne - g0 : kRowGroup;  // elements of this group
+    for (int g0 = 0; g0 < ne; g0 += GRP) {
+      const int ng = ne - g0 < GRP ? ne - g0 : GRP;  // elements of this group
       const int le = g0 + (eg < ng ? eg : 0);                    // idle lanes repeat a live element
-      R dna[2][16], acc[2][NEN], facc[2];
+      R acc[Z][NEN], facc[Z];
 #pragma unroll
-      for (int z = 0; z < 2; ++z) {
-#pragma unroll
-        for (int u = 0; u < 16 / PER; ++u) {
-          const V x = reinterpret_cast<const V*>(dn + DL * (an + HN * z))[u];
-#pragma unroll
-          for (int t = 0; t < PER; ++t) dna[z][PER * u + t] = x[t];
-        }
+      for (int z = 0; z < Z; ++z) {
 #pragma unroll
         for (int b = 0; b < NEN; ++b) acc[z][b] = R(0);
         facc[z] = R(0);
       }
       const R* base = rec + le * NQ * RS + kSlot * k;
+      const R* da = dn + DL * an;
       sfor<0, NQ>([&](auto qc) __attribute__((always_inline)) {
         constexpr int qq = decltype(qc)::value;
         Slot<R, true> sv;
         load_slot<R, true>(base + qq * RS, sv);
 #pragma unroll
-        for (int z = 0; z < 2; ++z)
-          contract_point<Rule, R, true, true, qq, NEN>(sv, dna[z][3 * qq], dna[z][3 * qq + 1], dna[z][3 * qq + 2], k,
-                                                       acc[z], facc[z]);
+        for (int z = 0; z < Z; ++z) {
+          const R* d = da + DL * HN * z + 3 * qq;
+          contract_point<Rule, R, true, true, qq, NEN>(sv, d[0], d[1], d[2], k, acc[z], facc[z]);
+        }
       });
-      R f1[2], f2[2];
+      R f1[Z], f2[Z];
 #pragma unroll
-      for (int z = 0; z < 2; ++z) {
+      for (int z = 0; z < Z; ++z) {
         f1[z] = __shfl_down(facc[z], 1, 64);
         f2[z] = __shfl_down(facc[z], 2, 64);
       }
       wave_sync();  // the previous rows have left the buffer
       if (eg < ng) {
 #pragma unroll
-        for (int z = 0; z < 2; ++z) {
+        for (int z = 0; z < Z; ++z) {
           R* row = stg + (NEN * eg + an + HN * z) * SS;
 #pragma unroll
           for (int u = 0; u < NEN / 2; ++u) {
@@ -1049,7 +1052,7 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
       wave_sync();
       constexpr int NP = kRowChunk / PER;  // pieces per row
 #pragma unroll
-      for (int u = 0; u < (kRowGroup * NEN * NP + 63) / 64; ++u) {
+      for (int u = 0; u < (GRP * NEN * NP + 63) / 64; ++u) {
         const int pc = lane + 64 * u, bl = pc / NP, pi = pc - bl * NP;
         if (bl < ng * NEN) {
           const R2* src = reinterpret_cast<const R2*>(stg + bl * SS + PER * pi);
@@ -1065,15 +1068,16 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
 }
 
 template <class Rule, typename R>
-__global__ __launch_bounds__(64, 2) void k_elem_rows(AsmArgs a, const int32_t* __restrict__ incpos,
-                                                    R* __restrict__ rows) {
-  const int64_t e0 = (int64_t)blockIdx.x * kRowElems;
-  elem_rows_tile<Rule, R>(a, incpos, rows, e0, (int)(a.n_elem - e0 < kRowElems ? a.n_elem - e0 : kRowElems));
+__global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows(AsmArgs a, int tile,
+                                                                           const int32_t* __restrict__ incpos,
+                                                                           R* __restrict__ rows) {
+  const int64_t e0 = (int64_t)blockIdx.x * tile;
+  elem_rows_tile<Rule, R>(a, incpos, rows, e0, (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile));
 }
 
 // many bodies: every body starts on a workgroup of its own, found by bisection
-template <class Rule>
-__global__ __launch_bounds__(64, 2) void k_elem_rows_batch(BatchArgs b) {
+template <class Rule, typename R>
+__global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows_batch(BatchArgs b) {
   const int64_t blk = blockIdx.x;
   int lo = 0, hi = b.n_bodies - 1;
   while (lo < hi) {
@@ -1082,9 +1086,9 @@ __global__ __launch_bounds__(64, 2) void k_elem_rows_batch(BatchArgs b) {
   }
   const BatchBody& B = b.bodies[lo];
   const AsmArgs a = body_args(b, B, lo);
-  const int64_t e0 = (blk - B.rblock_off) * kRowElems;
-  elem_rows_tile<Rule, float>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, e0,
-                              (int)(a.n_elem - e0 < kRowElems ? a.n_elem - e0 : kRowElems));
+  const int64_t e0 = (blk - B.rblock_off) * b.row_tile;
+  elem_rows_tile<Rule, R>(a, B.incpos, (R*)b.stage + B.blk_inc_off * kRowBlk, e0,
+                          (int)(a.n_elem - e0 < b.row_tile ? a.n_elem - e0 : b.row_tile));
 }
 
 // Persistent form of the batch (the LPT schedule): a grid sized to what the
@@ -1120,10 +1124,11 @@ __global__ void k_reset_counters(unsigned* counters) {
 }
 
 // Pass 2 over the row blocks: a lane per (incidence, row i, component k) task
-// of the range loads its ten K entries (three aligned 16-byte pieces of the
-// row, shifted by 2 values for k = 1) and adds them into the range's LDS
-// segment at row + 3 rank_b + k; the pieces of k = 2 end with the force entry.
-template <bool WANT_F, bool WANT_K, bool ACCUM>
+// of the range loads its ten K entries (aligned 16-byte pieces of the row:
+// five in float64, three in float32, shifted by 2 values for k = 1) and adds
+// them into the range's LDS segment at row + 3 rank_b + k; the force entry
+// follows those of k = 2 (in float32 in the same piece).
+template <typename R, bool WANT_F, bool WANT_K, bool ACCUM>
 __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int32_t I1, unsigned char* smem,
                                             int32_t* pre, int32_t* rowo) {
   constexpr int TPI = 9;
@@ -1147,8 +1152,10 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int
   if constexpr (WANT_K) add_mass_term<1>(g, I0, nn, lds, rowo);
   __syncthreads();
   const int ntask = pre[nn];
-  const float* blk = reinterpret_cast<const float*>(g.stage);
-  const f32x4* blkv = reinterpret_cast<const f32x4*>(g.stage);
+  using V = typename Vec4<R>::type;
+  constexpr int PER = (int)(sizeof(V) / sizeof(R)), NP = sizeof(R) == 4 ? 3 : kSlot / 2;
+  const R* blk = reinterpret_cast<const R*>(g.stage);
+  const V* blkv = reinterpret_cast<const V*>(g.stage);
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   for (int t = tid; t < ntask; t += blockDim.x) {
     const int jl = t / TPI, sl = t - TPI * jl, i = sl / 3, k = sl - 3 * i;
@@ -1156,19 +1163,27 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int
     const int rl = 3 * incn[jl] + i;
     if constexpr (WANT_K) {
       // 16-byte units with 32-bit offsets (checked on the host)
-      const uint32_t p0 = j * (uint32_t)(kRowBlk / 4) + (uint32_t)((kRowChunk * i + kSlot * k) >> 2);
-      const f32x4 w[3] = {blkv[p0], blkv[p0 + 1], blkv[p0 + 2]};
+      const uint32_t p0 = j * (uint32_t)(kRowBlk / PER) + (uint32_t)((kRowChunk * i + kSlot * k) / PER);
+      V w[NP];
+#pragma unroll
+      for (int u = 0; u < NP; ++u) w[u] = blkv[p0 + u];
+      R fv = R(0);
+      if constexpr (WANT_F) {
+        if constexpr (sizeof(R) == 4) fv = w[2][2];
+        else if (k == 2) fv = blkv[p0 + NP][0];
+      }
       const u32x4 rw = *reinterpret_cast<const u32x4*>(g.rank + (size_t)j * 16);
-      const bool odd = k == 1;
+      const bool odd = sizeof(R) == 4 && k == 1;
       double* dstp = lds + rowo[rl] + k;
 #pragma unroll
       for (int b = 0; b < 10; ++b) {
-        const float lo = w[b >> 2][b & 3], hi = w[(b + 2) >> 2][(b + 2) & 3];
+        R v = w[b / PER][b % PER];
+        if constexpr (sizeof(R) == 4) v = odd ? w[(b + 2) / PER][(b + 2) % PER] : v;
         const int rank_b = (int)((rw[b >> 2] >> (8 * (b & 3))) & 255u);
-        atomicAdd(dstp + 3 * rank_b, (double)(odd ? hi : lo));
+        atomicAdd(dstp + 3 * rank_b, (double)v);
       }
       if constexpr (WANT_F)
-        if (k == 2) atomicAdd(lf + rl, (double)w[2][2]);
+        if (k == 2) atomicAdd(lf + rl, (double)fv);
     } else {
       if (k == 0) atomicAdd(lf + rl, (double)blk[(size_t)j * kRowBlk + kRowChunk * i + 3 * kSlot]);
     }
@@ -1181,15 +1196,16 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& g, int32_t I0, int
   }
 }
 
-template <bool WANT_F, bool WANT_K, bool ACCUM>
+template <typename R, bool WANT_F, bool WANT_K, bool ACCUM>
 __global__ __launch_bounds__(512) void k_gather_rows(GatherArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t pre[kMaxRangeNodes + 1];
   __shared__ int32_t rowo[kMaxRangeNodes * 3];
   const int r = remap_tile(blockIdx.x, gridDim.x);
-  gather_rows<WANT_F, WANT_K, ACCUM>(g, g.ranges[r], g.ranges[r + 1], smem, pre, rowo);
+  gather_rows<R, WANT_F, WANT_K, ACCUM>(g, g.ranges[r], g.ranges[r + 1], smem, pre, rowo);
 }
 
+template <typename R>
 __global__ __launch_bounds__(512) void k_gather_rows_batch(BatchArgs b) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t pre[kMaxRangeNodes + 1];
@@ -1201,11 +1217,11 @@ __global__ __launch_bounds__(512) void k_gather_rows_batch(BatchArgs b) {
   g.inc_off = B.inc_off;
   g.row_off = B.row_off;
   g.rank = B.rank_inc;
-  g.stage = (const float*)b.stage + B.blk_inc_off * kRowBlk;
+  g.stage = (const R*)b.stage + B.blk_inc_off * kRowBlk;
   g.f = b.f + B.dof_off;
   g.vals = b.vals + B.nnz_off;
   g.inc_cap = b.inc_cap;
-  gather_rows<true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
+  gather_rows<R, true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
 }
 
 // persistent form: ranges taken from a counter, largest first
@@ -1231,7 +1247,7 @@ __global__ __launch_bounds__(512) void k_gather_rows_batch_lpt(BatchArgs b, cons
     g.f = b.f + B.dof_off;
     g.vals = b.vals + B.nnz_off;
     g.inc_cap = b.inc_cap;
-    gather_rows<true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
+    gather_rows<float, true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
   }
 }
 
@@ -1912,10 +1928,25 @@ int launch_nodes_rule(const Mesh& m, const void* stage, double* f, double* vals,
   return TLFEA_OK;
 }
 
-// pass 2 over the element row blocks (addressed in 16-byte units with 32-bit offsets)
+// Elements per workgroup of `waves` waves: as few as give every SIMD of the GPU
+// (256 CUs x 4) a wave, then up to `most`.  A small mesh is bound by the chain
+// of one wave, which is as long as its tile; from 1,024 waves on the point work,
+// which a short tile leaves lanes idle for, counts more.
+int tile_for(int64_t n_elem, int most, int waves) {
+  const int64_t groups = 1024 / waves;
+  return (int)std::min<int64_t>(most, std::max<int64_t>(1, (n_elem + groups - 1) / groups));
+}
+
+// pass 2 addresses T10 row blocks in 16-byte units with 32-bit offsets
+bool rows_addressable(const Mesh& m, size_t value_bytes) {
+  return m.n_elem * m.n_pn * (int64_t)(kRowBlk * value_bytes / 16) < ((int64_t)1 << 32);
+}
+
+// pass 2 over the element row blocks
+template <typename R>
 int launch_rows_nodes(const Mesh& m, double* f, double* vals, bool accum, hipStream_t s, const GatherOptions& mt) {
   const bool want_f = f != nullptr, want_k = vals != nullptr;
-  if (m.n_elem * m.n_pn * (int64_t)(kRowBlk / 4) >= ((int64_t)1 << 32)) return TLFEA_ERR_TOO_LARGE;
+  if (!rows_addressable(m, sizeof(R))) return TLFEA_ERR_TOO_LARGE;
   GatherArgs g{};
   g.ranges = m.d_ranges;
   g.inc_off = m.d_inc_off;
@@ -1934,8 +1965,8 @@ int launch_rows_nodes(const Mesh& m, double* f, double* vals, bool accum, hipStr
   const dim3 grid((unsigned)m.n_ranges), blk(64 * m.tune.waves);
 #define TLFEA_GATHER(F, K, A)                                              \
   do {                                                                     \
-    if (int rc = allow_lds(k_gather_rows<F, K, A>, lds)) return rc;        \
-    hipLaunchKernelGGL((k_gather_rows<F, K, A>), grid, blk, lds, s, g);   \
+    if (int rc = allow_lds(k_gather_rows<R, F, K, A>, lds)) return rc;        \
+    hipLaunchKernelGGL((k_gather_rows<R, F, K, A>), grid, blk, lds, s, g);   \
   } while (0)
   if (want_k && want_f) {
     if (accum) TLFEA_GATHER(true, true, true); else TLFEA_GATHER(true, true, false);
@@ -2069,12 +2100,30 @@ __global__ void k_zero(double* __restrict__ p, int64_t n) {
 
 }  // namespace
 
-bool use_rows(const Mesh& m, bool want_k) {
+static bool rows_on() {
   static const bool on = [] {
     const char* v = std::getenv("TLFEA_ELEMENT_ROWS");
     return !(v && v[0] == '0');
   }();
-  return on && want_k && m.precision == TLFEA_MIXED && m.d_incpos && (m.elem_type != TLFEA_T10 || m.d_rank_inc);
+  return on;
+}
+
+// float64 element rows (T10): pass 1 has one wave per SIMD and writes 3.7 GB of
+// blocks for 480,000 elements, pass 2 reads each once; point records are half
+// that size, but pass 2 reads them 6.5 times.  Whole call, rows against records:
+// 30,000 elements 148 / 144 us, 60,000 271 / 311, 480,000 2,070 / 2,382: the line
+// is at four rounds of 1,024 waves.  Undamped meshes keep the symmetric records
+// (480,000: 2,014 / 1,795).
+constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
+
+bool use_rows_batch(const Mesh& m, int64_t n_elem) {
+  if (!rows_on() || !m.d_incpos || (m.elem_type == TLFEA_T10 && !m.d_rank_inc)) return false;
+  if (m.precision == TLFEA_MIXED) return true;
+  return m.elem_type == TLFEA_T10 && n_elem >= kRows64MinElems && rows_addressable(m, sizeof(double));
+}
+
+bool use_rows(const Mesh& m, bool want_k) {
+  return want_k && use_rows_batch(m, m.n_elem) && (m.precision == TLFEA_MIXED || !sym_records(m));
 }
 
 // The float64 point records of a tangent pass take the symmetric layout for
@@ -2092,23 +2141,21 @@ bool use_force_blocks(const Mesh& m, bool want_k) {
 }
 
 size_t stage_bytes(const Mesh& m, bool want_k) {
-  if (use_rows(m, want_k))
-    return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * sizeof(float);
   const size_t r = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
+  if (use_rows(m, want_k)) return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * r;
   if (use_force_blocks(m, want_k)) return (size_t)m.n_elem * m.n_pn * 3 * m.mc * r;
   return (size_t)m.n_elem * m.n_qp * (want_k ? kRecK : kRecF) * r;
 }
 
-size_t row_block_bytes() { return kRowBlk * sizeof(float); }
 int lpt_tile_elems() { return kLptTile; }
 
-size_t row_block_bytes_for(int elem_type, int gl0) {
-  if (elem_type == TLFEA_T10) return row_block_bytes();
-  if (elem_type == TLFEA_ANCF3243) return rows_mc_block<RuleBeam::NEN>() * sizeof(float);
-  return rows_mc_block<16>() * sizeof(float);
+size_t row_block_bytes_for(int elem_type, int precision) {
+  const size_t r = precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
+  if (elem_type == TLFEA_T10) return kRowBlk * r;
+  return (elem_type == TLFEA_ANCF3243 ? rows_mc_block<RuleBeam::NEN>() : rows_mc_block<16>()) * r;
 }
-int row_elems_for(int elem_type, int gl0) {
-  if (elem_type == TLFEA_T10) return kRowElems;
+int row_elems_for(int elem_type, int gl0, int64_t n_elem) {
+  if (elem_type == TLFEA_T10) return tile_for(n_elem, kRowElems, 1);
   if (elem_type == TLFEA_ANCF3243) return rows_mc_elems<RuleBeam>();
   return gl0 == 3 ? rows_mc_elems<RuleAncf<3, 3, 2>>() : rows_mc_elems<RuleAncf<4, 4, 3>>();
 }
@@ -2154,16 +2201,20 @@ int launch_points(const Mesh& m, const AsmArgs& a, bool want_k, hipStream_t s) {
     return launch_rows_mc_points<RuleAncf<4, 4, 3>>(m, a, s);
   }
   if (use_rows(m, want_k)) {
-    const bool sym = sym_records(m);
-    const int64_t eb = sym ? kSymElems : kRowElems, blocks = (m.n_elem + eb - 1) / eb;
+    const bool sym = m.precision == TLFEA_MIXED && sym_records(m);
+    const int tile = tile_for(m.n_elem, sym ? kSymElems : kRowElems, sym ? kSymThreads / 64 : 1);
+    const int64_t blocks = (m.n_elem + tile - 1) / tile;
     if (blocks > INT32_MAX) return TLFEA_ERR_TOO_LARGE;
     if (blocks > 0) {
       if (sym)
-        hipLaunchKernelGGL(k_elem_rows_sym<RuleT10>, dim3((unsigned)blocks), dim3(kSymThreads), 0, s, a, m.d_incpos,
+        hipLaunchKernelGGL(k_elem_rows_sym<RuleT10>, dim3((unsigned)blocks), dim3(kSymThreads), 0, s, a, tile, m.d_incpos,
+                           (float*)m.d_stage);
+      else if (m.precision == TLFEA_MIXED)
+        hipLaunchKernelGGL((k_elem_rows<RuleT10, float>), dim3((unsigned)blocks), dim3(64), 0, s, a, tile, m.d_incpos,
                            (float*)m.d_stage);
       else
-        hipLaunchKernelGGL((k_elem_rows<RuleT10, float>), dim3((unsigned)blocks), dim3(64), 0, s, a, m.d_incpos,
-                           (float*)m.d_stage);
+        hipLaunchKernelGGL((k_elem_rows<RuleT10, double>), dim3((unsigned)blocks), dim3(64), 0, s, a, tile, m.d_incpos,
+                           (double*)m.d_stage);
     }
     TLFEA_HIP_CHECK(hipGetLastError());
     return TLFEA_OK;
@@ -2183,7 +2234,9 @@ int launch_nodes(const Mesh& m, double* f, double* vals, bool accum, hipStream_t
   if (m.staged == 3 && m.elem_type == TLFEA_ANCF3443)
     return m.gl[0] == 3 ? launch_rows_mc_nodes<RuleAncf<3, 3, 2>>(m, f, vals, accum, s, mt)
                         : launch_rows_mc_nodes<RuleAncf<4, 4, 3>>(m, f, vals, accum, s, mt);
-  if (m.staged == 3) return launch_rows_nodes(m, f, vals, accum, s, mt);
+  if (m.staged == 3)
+    return m.precision == TLFEA_MIXED ? launch_rows_nodes<float>(m, f, vals, accum, s, mt)
+                                      : launch_rows_nodes<double>(m, f, vals, accum, s, mt);
   if (m.staged == 4) return vals ? TLFEA_ERR_INVALID : launch_force_sum(m, m.d_stage, f, accum, s);
   if (m.precision == TLFEA_MIXED) return launch_nodes_prec<float>(m, f, vals, accum, s, mt);
   return launch_nodes_prec<double>(m, f, vals, accum, s, mt);
@@ -2267,6 +2320,18 @@ int launch_block_sum(const Mesh& m, const double* blk, double* out, hipStream_t 
   return TLFEA_OK;
 }
 
+template <typename R>
+int launch_rows_batch(const GatherTuning& tu, const BatchArgs& b, int n_ranges, size_t lds, hipStream_t s) {
+  if (b.n_rblocks > 0)
+    hipLaunchKernelGGL((k_elem_rows_batch<RuleT10, R>), dim3((unsigned)b.n_rblocks), dim3(64), 0, s, b);
+  TLFEA_HIP_CHECK(hipGetLastError());
+  const size_t lds_all = lds + b.inc_cap;
+  if (int rc = allow_lds(k_gather_rows_batch<R>, lds_all)) return rc;
+  hipLaunchKernelGGL(k_gather_rows_batch<R>, dim3(n_ranges), dim3(64 * tu.waves), lds_all, s, b);
+  TLFEA_HIP_CHECK(hipGetLastError());
+  return TLFEA_OK;
+}
+
 template <class Rule>
 int launch_rows_mc_batch(const GatherTuning& tu, const BatchArgs& b, int n_ranges, size_t lds, hipStream_t s) {
   constexpr bool MF = Rule::NEN == 16;  // the shell's slot tiles on the matrix cores
@@ -2312,17 +2377,9 @@ int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, 
     if (gl0 == 3) return launch_rows_mc_batch<RuleAncf<3, 3, 2>>(tu, b, n_ranges, lds, s);
     return launch_rows_mc_batch<RuleAncf<4, 4, 3>>(tu, b, n_ranges, lds, s);
   }
-  if (b.rows) {
-    if (b.n_rblocks > 0)
-      hipLaunchKernelGGL(k_elem_rows_batch<RuleT10>, dim3((unsigned)b.n_rblocks), dim3(64), 0, s, b);
-    TLFEA_HIP_CHECK(hipGetLastError());
-    const size_t lds_all = lds + b.inc_cap;
-    if (int rc = allow_lds(k_gather_rows_batch, lds_all)) return rc;
-    hipLaunchKernelGGL(k_gather_rows_batch, dim3(n_ranges), dim3(64 * tu.waves), lds_all, s, b);
-    TLFEA_HIP_CHECK(hipGetLastError());
-    return TLFEA_OK;
-  }
   const bool mixed = precision == TLFEA_MIXED;
+  if (b.rows)
+    return mixed ? launch_rows_batch<float>(tu, b, n_ranges, lds, s) : launch_rows_batch<double>(tu, b, n_ranges, lds, s);
   if (elem_type == TLFEA_T10)
     return mixed ? launch_batch_rule<RuleT10, float>(tu, b, n_ranges, lds, s)
                  : launch_batch_rule<RuleT10, double>(tu, b, n_ranges, lds, s);

@@ -34,6 +34,7 @@ struct tlfea_batch_s {
   int64_t n_points = 0, n_blocks = 0;
   int rows = 0;                      // element-row path (mixed; persistent schedule for T10)
   int64_t n_inc = 0, n_rblocks = 0;  // its row blocks and pass-1 workgroups
+  int row_tile = 1;                  // elements of a pass-1 workgroup
   size_t lds = 0;
   int inc_cap = 0;
   void* d_stage = nullptr;
@@ -89,12 +90,17 @@ static int upload(T*& d, size_t& cap, const std::vector<T>& h) {
   return TLFEA_OK;
 }
 
+// the persistent schedule is built for T10 element rows in mixed precision
+static bool has_lpt(const tlfea_batch_s* b) {
+  return b->rows && b->elem_type == TLFEA_T10 && b->precision == TLFEA_MIXED;
+}
+
 // The persistent (LPT) schedule of the element-row batch: every body's tiles of
 // tile_elems elements, full tiles of the largest bodies first and partial tiles
 // last; the ranges by decreasing work (incidences, then rows); grids of as
 // many workgroups as the GPU holds at once.
 static int batch_plan_lpt(tlfea_batch_s* b, int tile_elems) {
-  if (!b->rows || b->elem_type != TLFEA_T10) return TLFEA_ERR_UNSUPPORTED;
+  if (!has_lpt(b)) return TLFEA_ERR_UNSUPPORTED;
   if (tile_elems != 16 && tile_elems != tlfea::lpt_tile_elems()) return TLFEA_ERR_INVALID;
   struct Tile {
     int64_t work, body_size;
@@ -243,8 +249,11 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
   b->gl0 = m0.gl[0];
   b->precision = m0.precision;
   b->rows = 1;
+  int64_t n_elem = 0;
+  for (int i = 0; i < n_bodies; ++i) n_elem += meshes[i]->m.n_elem;
+  b->row_tile = tlfea::row_elems_for(b->elem_type, b->gl0, n_elem);
   for (int i = 0; i < n_bodies; ++i)
-    b->rows &= tlfea::use_rows(meshes[i]->m, true) ? 1 : 0;
+    b->rows &= tlfea::use_rows_batch(meshes[i]->m, n_elem) ? 1 : 0;
   std::vector<BatchBody> bodies(n_bodies);
   b->dof_off.assign(n_bodies + 1, 0);
   b->nnz_off.assign(n_bodies + 1, 0);
@@ -280,11 +289,10 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
     b->n_points += m.n_elem * m.n_qp;
     b->n_blocks += (m.n_elem * m.n_qp + tlfea::kStageThreads - 1) / tlfea::kStageThreads;
     b->n_inc += m.n_elem * m.n_pn;
-    const int reb = tlfea::row_elems_for(b->elem_type, b->gl0);
-    b->n_rblocks += (m.n_elem + reb - 1) / reb;
+    b->n_rblocks += (m.n_elem + b->row_tile - 1) / b->row_tile;
     // pass 2 addresses a body's row blocks in 16-byte units with 32-bit offsets
     if (b->rows && b->elem_type == TLFEA_T10 &&
-        m.n_elem * m.n_pn * (int64_t)(tlfea::row_block_bytes() / 16) >= ((int64_t)1 << 32)) {
+        m.n_elem * m.n_pn * (int64_t)(tlfea::row_block_bytes_for(b->elem_type, b->precision) / 16) >= ((int64_t)1 << 32)) {
       delete b;
       return TLFEA_ERR_TOO_LARGE;
     }
@@ -297,7 +305,7 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
     b->generation.push_back(m.generation);
   }
   if (b->n_blocks > INT32_MAX || b->n_rblocks > INT32_MAX) { delete b; return TLFEA_ERR_TOO_LARGE; }
-  const size_t stage = b->rows ? (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->gl0)
+  const size_t stage = b->rows ? (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->precision)
                                : (size_t)b->n_points * tlfea::stage_record_bytes(b->precision);
   if (hipSetDevice(b->device) != hipSuccess) { delete b; return TLFEA_ERR_HIP; }
   if (hipMalloc(&b->d_bodies, sizeof(BatchBody) * bodies.size()) != hipSuccess ||
@@ -365,6 +373,7 @@ static BatchArgs batch_args(tlfea_batch_t b, const double* d_q, const double* d_
   a.n_points = b->n_points;
   a.n_blocks = b->n_blocks;
   a.n_rblocks = b->n_rblocks;
+  a.row_tile = b->row_tile;
   a.rows = b->rows;
   a.inc_cap = b->inc_cap;
   a.stage = b->d_stage;
@@ -455,7 +464,7 @@ TLFEA_API int tlfea_batch_get_gather_shape(tlfea_batch_t b, tlfea_gather_shape* 
 TLFEA_API int tlfea_batch_set_schedule(tlfea_batch_t b, int32_t persistent, int32_t tile_elems) {
   if (!b || (persistent != 0 && persistent != 1)) return TLFEA_ERR_INVALID;
   if (!batch_current(b)) return TLFEA_ERR_INVALID;
-  if (persistent && !(b->rows && b->elem_type == TLFEA_T10)) return TLFEA_ERR_UNSUPPORTED;
+  if (persistent && !has_lpt(b)) return TLFEA_ERR_UNSUPPORTED;
   if (hipSetDevice(b->device) != hipSuccess) return TLFEA_ERR_HIP;
   return batch_set_schedule(b, persistent, tile_elems);
 }
@@ -465,7 +474,7 @@ TLFEA_API int tlfea_batch_get_schedule(tlfea_batch_t b, int32_t* persistent, int
   if (!b) return TLFEA_ERR_INVALID;
   const tlfea::BatchSchedule& sc = b->sched;
   if (persistent) *persistent = sc.persistent;
-  if (tile_elems) *tile_elems = sc.persistent ? sc.tile_elems : tlfea::row_elems_for(b->elem_type, b->gl0);
+  if (tile_elems) *tile_elems = sc.persistent ? sc.tile_elems : b->row_tile;
   if (grid_tiles) *grid_tiles = sc.persistent ? sc.grid_tiles : (int32_t)b->n_rblocks;
   if (grid_ranges) *grid_ranges = sc.persistent ? sc.grid_ranges : b->n_ranges;
   return TLFEA_OK;
@@ -484,7 +493,7 @@ TLFEA_API int tlfea_batch_autotune(tlfea_batch_t b, const double* d_q, const dou
     int persistent, tile_elems;
   };
   std::vector<Cand> cands{{0, tlfea::lpt_tile_elems()}};
-  if (b->rows && b->elem_type == TLFEA_T10) {
+  if (has_lpt(b)) {
     cands.push_back({1, tlfea::lpt_tile_elems()});
     cands.push_back({1, 16});
   }

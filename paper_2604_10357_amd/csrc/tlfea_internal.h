@@ -271,6 +271,7 @@ struct BatchArgs {
   int n_bodies;
   int64_t n_points, n_blocks;
   int64_t n_rblocks;  // pass-1 workgroups of the element-row path
+  int row_tile;       // T10: elements of each (ANCF tiles have a fixed size)
   int rows;           // 1: element-row path (T10, mixed), 0: per-point records
   void* stage;
   const double* q;
@@ -301,21 +302,23 @@ int batch_lpt_occupancy(int tile_elems, int waves, size_t lds_all, int* tiles_pe
 MatParams make_params(int material, const double* params, double eta, double lam_v);
 
 // bytes of pass-1 records for a mesh / per record
-// Element-row path: the tangent in mixed precision, every element type (the
-// environment variable TLFEA_ELEMENT_ROWS=0 switches it off; batches take it
-// for T10 only).  Pass 1 then leaves one row block per incidence instead of
-// per-point records.
+// Element-row path: the tangent in mixed precision, every element type, and of
+// large damped T10 meshes in float64 (the environment variable
+// TLFEA_ELEMENT_ROWS=0 switches it off).  Pass 1 then leaves one row block per
+// incidence instead of per-point records.
 bool use_rows(const Mesh& m, bool want_k);
+// the same for a member of a batch of n_elem elements in all (full tangent
+// layout, whatever the material)
+bool use_rows_batch(const Mesh& m, int64_t n_elem);
 bool point_records_sym(const Mesh& m, bool want_k);
 // Force-only path (every element type; TLFEA_FORCE_BLOCKS=0 switches it off):
 // pass 1 leaves one float-or-double force block of 3 mc values per incidence.
 bool use_force_blocks(const Mesh& m, bool want_k);
 size_t stage_bytes(const Mesh& m, bool want_k);
 size_t stage_record_bytes(int precision);
-size_t row_block_bytes();  // element-row path: bytes per (element, node) row block
 int lpt_tile_elems();      // elements per item of the persistent batch schedule (the default)
-size_t row_block_bytes_for(int elem_type, int gl0);  // the same per element type
-int row_elems_for(int elem_type, int gl0);           // elements per pass-1 workgroup
+size_t row_block_bytes_for(int elem_type, int precision);  // element-row path: bytes per (element, node) row block
+int row_elems_for(int elem_type, int gl0, int64_t n_elem);  // elements per pass-1 workgroup (n_elem: of the launch)
 int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tune, const BatchArgs& b,
                  int n_ranges, size_t lds, hipStream_t s, const BatchSchedule& sc);
 

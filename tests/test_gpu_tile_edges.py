@@ -9,6 +9,8 @@ import torch
 
 import oracle
 from paper_2604_10357_amd import workloads as W
+from paper_2604_10357_amd._native import TlfeaError
+from paper_2604_10357_amd.api import TLBatch
 from tests.gpu_util import TOL, cuda, make_mesh, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +55,45 @@ def test_t10_row_tiles(damped, n):
     assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
     assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
     m.close()
+
+
+def test_t10_float64_rows_and_records():
+    """float64 meshes above 49,152 damped elements take the element rows: a mesh
+    just above the line and its undamped form (point records) against the oracle,
+    in one batch with a small mesh and alone."""
+    print("[gpu] float64 rows", flush=True)
+    kv = W.Material(W.MOONEY_RIVLIN, (2e5, 5e4, 1e8), 1e3, 7e2)
+    big = W.t10_beam(2049, 2, 2, 180, "rows64", lx=25.6, ly=0.025, lz=0.025, material=kv)
+    big = first_elements(big, 49153)
+    small = W.t10_beam(3, 2, 2, 181, "rows64_small", material=kv)
+    refs, handles = [], []
+    for wl in (big, small):
+        om, mat = oracle.Mesh.of(wl.mesh), oracle.material_of(wl.material)
+        refs.append(oracle.assemble(om, mat, wl.q, wl.qdot, 1e-3, 1.0))
+        handles.append(make_mesh(wl, "fp64"))
+    for wl, m, (f_ref, v_ref) in zip((big, small), handles, refs):
+        f, v = m.assemble(cuda(wl.q), cuda(wl.qdot), 1e-3, 1.0)
+        f_only = torch.empty_like(f)
+        m.assemble_nodes(f_only)  # the force alone from the blocks
+        torch.cuda.synchronize()
+        assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+        assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["fp64"]
+        assert rel_err(f_only.cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+    b = TLBatch(handles)
+    q, qd = (cuda(np.concatenate([getattr(wl, k) for wl in (big, small)])) for k in ("q", "qdot"))
+    f, v = b.assemble(q, qd, torch.full((2,), 1e-3, dtype=torch.float64, device="cuda"))
+    torch.cuda.synchronize()
+    for i, (f_ref, v_ref) in enumerate(refs):
+        assert rel_err(f[b.dof_off[i]:b.dof_off[i + 1]].cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+        assert rel_err(v[b.nnz_off[i]:b.nnz_off[i + 1]].cpu().numpy(), v_ref)[0] <= TOL["fp64"]
+    with pytest.raises(TlfeaError):  # the persistent schedule is for mixed batches
+        b.set_schedule(True, 25)
+    b.close()
+    handles[0].set_material(W.Material(W.MOONEY_RIVLIN, (2e5, 5e4, 1e8)))
+    om = oracle.Mesh.of(big.mesh)
+    f_ref, v_ref = oracle.assemble(om, oracle.material_of(handles[0].material), big.q, big.qdot, 1e-3, 1.0)
+    f, v = handles[0].assemble(cuda(big.q), cuda(big.qdot), 1e-3, 1.0)
+    torch.cuda.synchronize()
+    assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["fp64"] and rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["fp64"]
+    for m in handles:
+        m.close()
