@@ -343,8 +343,8 @@ int tlfea_newton_gradient(tlfea_mesh_t mesh, const double* d_v, const double* d_
  * caller memory (moments, gradient, internal force; the gradient is left at
  * d_work + 2 n_dof).  iters_out / gnorm_out (host, may be NULL): iterations
  * run and the last ||g||.  Needs tlfea_build_mass; `stream` must not be the
- * legacy default stream (the iterations between checks are captured into a
- * HIP graph).  Synchronises at every check. */
+ * legacy default stream (in a long solve the iterations between checks are
+ * captured into a HIP graph).  Synchronises at every check. */
 typedef struct {
   double lr;           /* step size alpha */
   double beta1, beta2; /* moment decay rates, in [0, 1) */

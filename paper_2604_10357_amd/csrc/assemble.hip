@@ -2278,15 +2278,21 @@ int launch_force_noalloc(const Mesh& m, const AsmArgs& a, double* f, hipStream_t
   return launch_force_sum(m, blk, f, false, s);
 }
 
-int launch_force_blocks(Mesh& m, const AsmArgs& a, double* f, hipStream_t s) {
+int launch_force_points(Mesh& m, const AsmArgs& a, hipStream_t s) {
+  if (m.n_elem == 0) return TLFEA_OK;  // no blocks
   if (!m.d_incpos) return TLFEA_ERR_NO_PATTERN;
   const size_t rsz = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
   if (int rc = ensure_stage(m, (size_t)m.n_elem * m.n_pn * 3 * m.mc * rsz)) return rc;
-  int rc = m.precision == TLFEA_MIXED ? launch_force_prec<float>(m, a, m.d_stage, s)
-                                      : launch_force_prec<double>(m, a, m.d_stage, s);
+  const int rc = m.precision == TLFEA_MIXED ? launch_force_prec<float>(m, a, m.d_stage, s)
+                                            : launch_force_prec<double>(m, a, m.d_stage, s);
   m.staged = rc ? 0 : 4;
   m.staged_precision = m.precision;
-  if (rc) return rc;
+  return rc;
+}
+
+int launch_force_blocks(Mesh& m, const AsmArgs& a, double* f, hipStream_t s) {
+  if (!m.d_incpos) return TLFEA_ERR_NO_PATTERN;
+  if (int rc = launch_force_points(m, a, s)) return rc;
   return launch_force_sum(m, m.d_stage, f, false, s);
 }
 

@@ -183,10 +183,14 @@ __global__ void k_vdiff(const double* v, const double* vp, int64_t n, double* dv
 
 // T10 (about 28 neighbours per node) gathers v - v_prev formed once per DOF
 // (dv, vp null); ANCF (3 or 9) forms the difference at each gather.
-template <int MC>
+// SUM: f_int is not given but summed here from the element force blocks of the
+// node's incidences (3 MC values each, node-sorted), spread over the group's
+// lanes, reduced beside the mass row and written to fint.
+template <int MC, bool SUM, typename R>
 __global__ __launch_bounds__(256) void k_gradient(const int32_t* adj_off, const int32_t* adj, const double* mass,
                                                   int64_t n_nodes, const double* dv, const double* vp,
-                                                  const double* fint, const double* fext, double inv_h, double* g) {
+                                                  double* fint, const double* fext, double inv_h, double* g,
+                                                  const int32_t* __restrict__ inc_off, const R* __restrict__ blocks) {
   constexpr int NR = 3 * MC;  // rows per node: (coefficient k, component d) at 3 k + d
   constexpr int LANES = grad_lanes<MC>(), UNR = TLFEA_GRAD_UNROLL;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -225,25 +229,81 @@ __global__ __launch_bounds__(256) void k_gradient(const int32_t* adj_off, const 
       }
     }
   }
+  double fs[SUM ? NR : 1];
+  if constexpr (SUM) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j) fs[j] = 0.0;
+    if (I < n_nodes) {
+      const int32_t x1 = inc_off[I + 1];
+      for (int32_t x = inc_off[I] + sub; x < x1; x += LANES) {
+        const R* b = blocks + (int64_t)x * NR;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) fs[j] += (double)b[j];
+      }
+    }
+  }
   // butterfly over the group: every lane ends with the full sums (all lanes
   // take part; groups never straddle a wave)
 #pragma unroll
   for (int o = LANES / 2; o > 0; o >>= 1)
 #pragma unroll
-    for (int j = 0; j < NR; ++j) s[j] += __shfl_xor(s[j], o, LANES);
+    for (int j = 0; j < NR; ++j) {
+      s[j] += __shfl_xor(s[j], o, LANES);
+      if constexpr (SUM) fs[j] += __shfl_xor(fs[j], o, LANES);
+    }
   if (I < n_nodes) {
 #pragma unroll
     for (int j = 0; j < NR; ++j)
       if (j % LANES == sub) {
         const int64_t r = NR * I + j;
-        g[r] = s[j] * inv_h + fint[r] - (fext ? fext[r] : 0.0);
+        double fr;
+        if constexpr (SUM) {
+          fr = fs[j];
+          fint[r] = fr;
+        } else {
+          fr = fint[r];
+        }
+        g[r] = s[j] * inv_h + fr - (fext ? fext[r] : 0.0);
       }
   }
 }
 
 int blocks_of(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
+template <int MC, bool SUM, typename R>
+void launch_gradient(const Mesh& m, const double* dv, const double* vp, double* fint, const double* fext,
+                     double h, double* g, const R* blocks, hipStream_t s) {
+  hipLaunchKernelGGL((k_gradient<MC, SUM, R>), dim3(blocks_of(m.n_pnodes * grad_lanes<MC>(), 256)), dim3(256), 0, s,
+                     m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes, dv, vp, fint, fext, 1.0 / h, g, m.d_inc_off, blocks);
+}
+
 }  // namespace
+
+int ensure_dv(Mesh& m) {
+  if (m.mc != 1 || m.d_dv || m.n_dof == 0) return TLFEA_OK;
+  if (hipMalloc(&m.d_dv, sizeof(double) * m.n_dof) != hipSuccess) {
+    (void)hipGetLastError();
+    m.d_dv = nullptr;
+    return TLFEA_ERR_NOMEM;
+  }
+  return TLFEA_OK;
+}
+
+int launch_gradient_blocks(Mesh& m, const double* v, const double* v_prev, const double* f_ext, double h, double* f,
+                           double* g, hipStream_t s) {
+  if (m.n_pnodes == 0) return TLFEA_OK;
+  const double* dv = m.mc == 1 ? m.d_dv : v;
+  if (m.precision == TLFEA_MIXED) {
+    if (m.mc == 1) launch_gradient<1, true>(m, dv, nullptr, f, f_ext, h, g, (const float*)m.d_stage, s);
+    else launch_gradient<4, true>(m, dv, v_prev, f, f_ext, h, g, (const float*)m.d_stage, s);
+  } else {
+    if (m.mc == 1) launch_gradient<1, true>(m, dv, nullptr, f, f_ext, h, g, (const double*)m.d_stage, s);
+    else launch_gradient<4, true>(m, dv, v_prev, f, f_ext, h, g, (const double*)m.d_stage, s);
+  }
+  TLFEA_HIP_CHECK(hipGetLastError());
+  return TLFEA_OK;
+}
+
 }  // namespace tlfea
 
 static int mass_ready(tlfea_mesh_t mesh) {
@@ -318,22 +378,12 @@ TLFEA_API int tlfea_newton_gradient(tlfea_mesh_t mesh, const double* d_v, const 
   const auto s = (hipStream_t)stream;
   if (m.mc == 1) {
     // v - v_prev once per DOF, so that the neighbour gathers read one vector
-    if (!m.d_dv) {
-      if (hipMalloc(&m.d_dv, sizeof(double) * m.n_dof) != hipSuccess) {
-        (void)hipGetLastError();
-        m.d_dv = nullptr;
-        return TLFEA_ERR_NOMEM;
-      }
-    }
+    if ((rc = tlfea::ensure_dv(m))) return rc;
     hipLaunchKernelGGL(tlfea::k_vdiff, dim3(tlfea::blocks_of(m.n_dof, 256)), dim3(256), 0, s, d_v, d_v_prev,
                        m.n_dof, m.d_dv);
-    hipLaunchKernelGGL(tlfea::k_gradient<1>, dim3(tlfea::blocks_of(m.n_pnodes * tlfea::grad_lanes<1>(), 256)),
-                       dim3(256), 0, s, m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes, m.d_dv, nullptr, d_f_int,
-                       d_f_ext, 1.0 / h, d_g);
+    tlfea::launch_gradient<1, false, double>(m, m.d_dv, nullptr, const_cast<double*>(d_f_int), d_f_ext, h, d_g, nullptr, s);
   } else {
-    hipLaunchKernelGGL(tlfea::k_gradient<4>, dim3(tlfea::blocks_of(m.n_pnodes * tlfea::grad_lanes<4>(), 256)),
-                       dim3(256), 0, s, m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes, d_v, d_v_prev, d_f_int,
-                       d_f_ext, 1.0 / h, d_g);
+    tlfea::launch_gradient<4, false, double>(m, d_v, d_v_prev, const_cast<double*>(d_f_int), d_f_ext, h, d_g, nullptr, s);
   }
   TLFEA_HIP_CHECK(hipGetLastError());
   return TLFEA_OK;

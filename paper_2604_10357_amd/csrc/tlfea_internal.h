@@ -191,7 +191,8 @@ struct Mesh {
   int32_t* d_cols_u = nullptr;
   int64_t nnz_u = -1;
   double density = 0.0;           // of the mass above (0: not built)
-  double* d_solver = nullptr;     // first-order solver: iteration counter, bias corrections, norm partials, norms
+  double* d_solver = nullptr;     // first-order solver: iteration counter, norm partials, norms, bias corrections
+  size_t solver_cap = 0;          // doubles it holds
   double* d_dv = nullptr;         // gradient: v - v_prev per DOF (allocated by the first call)
   hipStream_t last_stream = nullptr;
 };
@@ -360,6 +361,15 @@ size_t noalloc_force_bytes(const Mesh& m);
 int launch_force_noalloc(const Mesh& m, const AsmArgs& a, double* f, hipStream_t s);
 // the force-block path with the mesh's work buffer (force only, pattern needed)
 int launch_force_blocks(Mesh& m, const AsmArgs& a, double* f, hipStream_t s);
+// its pass 1 alone (the blocks stay in the work buffer)
+int launch_force_points(Mesh& m, const AsmArgs& a, hipStream_t s);
+
+// gradient g = M (v - v_prev) / h + f_int - f_ext with f_int summed from the
+// force blocks in the work buffer and written to f; T10: v - v_prev is in m.d_dv
+// (newton.hip)
+int launch_gradient_blocks(Mesh& m, const double* v, const double* v_prev, const double* f_ext, double h, double* f,
+                           double* g, hipStream_t s);
+int ensure_dv(Mesh& m);  // m.d_dv allocated (T10)
 // material constants of a device parameter vector (p0, p1, p2, kv_eta, kv_lambda) -> m.d_mp
 int launch_params(const Mesh& m, const double* d_params, hipStream_t s);
 

@@ -88,3 +88,34 @@ def test_adamw_stops_and_rejects():
         m.adamw_solve(q_n, cuda(v_n), cuda(v_n.copy()), H, 1e-3)
     assert e.value.status == -1
     m.close()
+
+
+@pytest.mark.parametrize("kind,precision", [("t10", "fp64"), ("t10", "mixed"), ("beam", "fp64")])
+def test_adamw_replayed_and_launched(kind, precision):
+    """A solve long enough to replay its iterations from a graph (checks every 3,
+    40 iterations: 13 replays and a shorter rest) against the oracle, and the
+    internal force left beside the gradient."""
+    print(f"[gpu] adamw replay {kind} {precision}", flush=True)
+    wl, v_n, f_ext = problem(113, kind)
+    m = make_mesh(wl, precision)
+    m.build_mass(RHO)
+    prm = (2e-3, 0.9, 0.999, 1e-8, 0.01)
+    om = oracle.Mesh.of(wl.mesh)
+    pat = oracle.csr_pattern(om)
+    v_ref, q_ref, g_ref = oracle.adamw_solve(om, oracle.material_of(wl.material), pat, oracle.mass_csr(om, RHO, pat),
+                                             wl.q, v_n, f_ext, v_n, H, *prm, 40)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    with torch.cuda.stream(s):
+        for _ in range(2):  # the second solve finds the first one's buffers
+            work = torch.empty(4 * m.n_dof, dtype=torch.float64, device="cuda")
+            v, q, done, _, g = m.adamw_solve(cuda(wl.q), cuda(v_n), cuda(v_n.copy()), H, *prm, f_ext=cuda(f_ext),
+                                             max_iters=40, check_every=3, work=work)
+            f = m.internal_force(q, v)
+            s.synchronize()
+            assert done == 40
+            assert np.abs(v.cpu().numpy() - v_ref).max() <= tol * np.abs(v_ref - v_n).max()
+            assert rel_err(g.cpu().numpy(), g_ref)[0] <= tol
+            assert rel_err(work[3 * m.n_dof:].cpu().numpy(), f.cpu().numpy())[0] <= 1e-13
+    m.close()
