@@ -53,6 +53,7 @@ constexpr int kRecF = 12;  // force-only record: Phat_ik at 4 i + k
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <typename T>
 struct Vec4 { using type = f32x4; };
 template <>
@@ -1272,6 +1273,19 @@ constexpr int rows_mc_elems() { return kRowsMcThreads / Rule::NQ; }
 template <int NEN>
 constexpr int rows_mc_block() { return 36 * NEN + 36; }
 
+// What phase B needs of its elements from global memory, read before the first
+// store: loads and stores retire in one order, so a load between the stores of
+// two tasks would wait for the earlier ones to reach memory.
+template <class Rule, int EB>
+struct RowsOut {
+  double sc[4 * EB];             // coefficient scales by kind
+  int32_t ip[Rule::NPN * EB];    // places of the element's incidences
+  __device__ __forceinline__ void fill(const AsmArgs& a, const int32_t* __restrict__ incpos, int64_t e0, int ne) {
+    for (int t = threadIdx.x; t < Rule::NPN * ne; t += blockDim.x) ip[t] = incpos[e0 * Rule::NPN + t];
+    for (int le = threadIdx.x; le < ne; le += blockDim.x) element_scales<Rule>(a, e0 + le, sc + 4 * le);
+  }
+};
+
 // Phase B of the ANCF element rows for a symmetric tangent (undamped
 // materials): only the slots i <= k are contracted, a lane per task (element,
 // slot, coefficient a), coefficients fastest.  A task writes its NEN entries
@@ -1586,11 +1600,268 @@ __global__ __launch_bounds__(kRowsMcThreads) void k_elem_rows_mc_batch(BatchArgs
                                      blk - B.rblock_off);
 }
 
+// The float64 form.  A point's tangent takes 250 registers, so two waves run per
+// SIMD, and as for T10 the factors stay in registers and LDS holds the slots of
+// one row component i at a time (240 bytes per point).  Elements per workgroup:
+// whole elements in one wave (beam, 60 lanes), two (3x3x2 shell, 126) or four
+// (4x4x3, 240).  Against point records, which pass 2 read once per node of the
+// element, the whole call: 500,000 beams 2,825 -> 2,140 us, 65,536 3x3x2 shells
+// 1,166 -> 1,003 (damped 1,510 -> 1,068), 10,000 4x4x3 shells 434 -> 257 (605 ->
+// 291).  Bound by the phases in turn, which two waves overlap little: of the
+// beams' 1,343 us in pass 1 the points take 380, the contraction 380 and the
+// 2.6 GB of stores the rest; of the 65,536 shells' 611 the points take 290.
+template <class Rule>
+constexpr int rows64_threads() { return Rule::NQ == 48 ? 256 : Rule::NQ == 18 ? 128 : 64; }
+template <class Rule>
+constexpr int rows64_elems() { return rows64_threads<Rule>() / Rule::NQ; }
+
+// Value of lane C of the lane's row of 16.
+template <int C>
+__device__ __forceinline__ double row_lane(double v) {
+  return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + C, 0xf, 0xf, true);
+}
+
+// One row component i of the beam's elements: a lane per (element, component k,
+// kind of coefficient) takes the coefficients of both nodes, which reads a slot
+// once for two rows, over all points.  The column gradients are wave-uniform and
+// come through the scalar cache; those that vanish at every point are skipped.
+// The rows go through LDS, so that a store writes 192 consecutive bytes (straight
+// from the lanes, 16 bytes every 64: pass 1 1,381 us, with non-temporal stores
+// 3,700; through LDS 1,343).
+template <class Rule, int I, int EB>
+__device__ __forceinline__ void rows64_vector(const RowsOut<Rule, EB>& ro, double* __restrict__ rows, int ne,
+                                              double* rec, const double* dn, double* fst) {
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, TH = rows64_threads<Rule>();
+  constexpr int BLK = rows_mc_block<NEN>(), RS = 3 * kSlot, Z = 2, NA = NEN / Z;
+  const int tid = threadIdx.x, ntask = ne * NA * 3;
+  static_assert(EB * NA * 3 <= TH, "a lane per task");
+  {
+    const bool on = tid < ntask;
+    const int t = on ? tid : ntask - 1;
+    const int le = t / (3 * NA), r = t - 3 * NA * le, al = r / 3, k = r - 3 * al;
+    double acc[Z][NEN], facc[Z];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) {
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) acc[z][b] = 0.0;
+      facc[z] = 0.0;
+    }
+    const double* recp = rec + le * NQ * RS + kSlot * k;
+#pragma unroll 2
+    for (int qq = 0; qq < NQ; ++qq) {
+      Slot<double, true> sv;
+      load_slot<double, true>(recp + qq * RS, sv);
+#pragma unroll
+      for (int z = 0; z < Z; ++z) {
+        const double* d = dn + NEN * qq + al + NA * z;
+        const double d0 = d[0], d1 = d[NEN * NQ], d2 = d[2 * NEN * NQ];
+        double tn[3];
+#pragma unroll
+        for (int n = 0; n < 3; ++n) tn[n] = sv.v[n] * d0 + sv.v[3 + n] * d1 + sv.v[6 + n] * d2;
+        facc[z] += sv.v[9] * (k == 0 ? d0 : k == 1 ? d1 : d2);
+#pragma unroll
+        for (int b = 0; b < NEN; ++b)
+#pragma unroll
+          for (int n = 0; n < 3; ++n)
+            if (Rule::grad_nz(b, n)) acc[z][b] += tn[n] * Rule::dN_rt(qq, b, n);
+      }
+    }
+    const double* sc = ro.sc + 4 * le;
+    __syncthreads();  // the slots are consumed: the LDS takes the block rows [element][coefficient][k][b]
+    if (on) {
+#pragma unroll
+      for (int z = 0; z < Z; ++z) {
+        const int az = al + NA * z;
+        const double s_a = sc[az & 3];
+#pragma unroll
+        for (int u = 0; u < NEN / 2; ++u) {
+          f64x2 w;
+          w[0] = acc[z][2 * u] * s_a * sc[(2 * u) % 4];
+          w[1] = acc[z][2 * u + 1] * s_a * sc[(2 * u + 1) % 4];
+          *reinterpret_cast<f64x2*>(rec + ((le * NEN + az) * 3 + k) * NEN + 2 * u) = w;
+        }
+        fst[(le * NEN + az) * 9 + 3 * I + k] = facc[z] * s_a;
+      }
+    }
+    __syncthreads();
+    constexpr int PR = 3 * NEN / 2;  // pairs per row
+    for (int p = tid; p < ne * NEN * PR; p += TH) {
+      const int ra = p / PR, x = p - ra * PR, az = ra & (NEN - 1);
+      double* o = rows + (int64_t)ro.ip[ra >> 2] * BLK + (3 * (az & 3) + I) * 3 * NEN + 2 * x;
+      const f64x2 w = *reinterpret_cast<const f64x2*>(rec + ra * 3 * NEN + 2 * x);
+      *reinterpret_cast<f64x2*>(o) = w;
+    }
+    if (I == 2)
+      for (int p = tid; p < ne * NPN * 18; p += TH) {
+        const int in = p / 18, x = p - in * 18;
+        const f64x2 w = *reinterpret_cast<const f64x2*>(fst + in * 36 + 2 * x);
+        f64x2* o = reinterpret_cast<f64x2*>(rows + (int64_t)ro.ip[in] * BLK + 36 * NEN + 2 * x);
+        *o = w;
+      }
+  }
+}
+
+// One row component i of the shell's elements on the matrix cores: a wave takes
+// the 16 x 16 tile K^(ik)_ab = sum over (q, n) of T_n(q)[a] dN_b,n(q), T_n(q)[a] =
+// sum_m Ahat_q,imkn dN_a,m(q), as 16x16x4 products over four points per n (the
+// point axis is padded to a multiple of four with zeros).  Lane l is coefficient
+// l % 16 of both sides at point l / 16 of the four: the three gradients it reads
+// serve as A's factor and as B, and a slot value is read once per row of 16 lanes
+// and passed along the row, so a step reads four doubles per lane for three
+// products (the vector form: thirteen for 57 multiply-adds, bound by LDS; pass 1 of 65,536
+// 3x3x2 shells 835 us, so 611).  For an undamped material the slots i <= k alone
+// are multiplied and stored a second time, transposed.
+// Lane l then holds K^(ik)[l / 16 + 4 r][l % 16], r < 4: node r, kind l / 16.
+template <class Rule, bool SYM, int I, int EB>
+__device__ __forceinline__ void rows64_matrix(const RowsOut<Rule, EB>& ro, double* __restrict__ rows, int ne,
+                                              const double* rec, const double* dn) {
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, NW = rows64_threads<Rule>() / 64;
+  constexpr int BLK = rows_mc_block<NEN>(), RS = 3 * kSlot, NG = (NQ + 3) / 4;
+  static_assert(NEN == 16 && NPN == 4, "one 16 x 16 tile per slot");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = 4 * (lane & 3) + ((lane >> 2) & 3);
+  const int sl = (lane & 15) < kSlot ? lane & 15 : kSlot - 1;
+#pragma unroll 1
+  for (int t = wave; t < 3 * ne; t += NW) {  // uniform per wave
+    const int kk = t / ne, le = t - kk * ne;
+    const int k = I + kk < 3 ? I + kk : I + kk - 3;  // the slots k >= i first
+    const bool tile = !SYM || k >= I;
+    const double* re = rec + le * NQ * RS + kSlot * k + sl;
+    f64x4 acc{0.0, 0.0, 0.0, 0.0};
+    double facc = 0.0;
+    double d[3], v;
+    auto load = [&](int gq) __attribute__((always_inline)) {
+      const int q = 4 * gq + g;
+      const bool live = NQ % 4 == 0 || q < NQ;
+      const int qc = live ? q : NQ - 1;
+      const double* p = dn + NEN * qc + c;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) d[m] = p[m * NEN * NQ];
+      v = re[qc * RS];
+      if (!live) {
+        v = 0.0;
+#pragma unroll
+        for (int m = 0; m < 3; ++m) d[m] = 0.0;
+      }
+    };
+    load(0);
+#pragma unroll 4
+    for (int gq = 0; gq < NG; ++gq) {
+      const double d0 = d[0], d1 = d[1], d2 = d[2], vv = v;
+      if (gq + 1 < NG) load(gq + 1);
+      facc += row_lane<9>(vv) * (k == 0 ? d0 : k == 1 ? d1 : d2);
+      if (tile) {
+        const double t0 = row_lane<0>(vv) * d0 + row_lane<3>(vv) * d1 + row_lane<6>(vv) * d2;
+        const double t1 = row_lane<1>(vv) * d0 + row_lane<4>(vv) * d1 + row_lane<7>(vv) * d2;
+        const double t2 = row_lane<2>(vv) * d0 + row_lane<5>(vv) * d1 + row_lane<8>(vv) * d2;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t0, d0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t1, d1, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t2, d2, acc, 0, 0, 0);
+      }
+    }
+    facc += __shfl_xor(facc, 16);
+    facc += __shfl_xor(facc, 32);
+    const double* sc = ro.sc + 4 * le;
+    const int kc = c & 3;
+    const double s_c = sc[kc];
+    const int32_t* ip = ro.ip + NPN * le;
+    if (tile) {
+      double* ob = rows + (int64_t)ip[g] * BLK + (3 * I + k) * NEN + c;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc[r] *= sc[r] * s_c;
+        ob[9 * NEN * r] = acc[r];
+      }
+      if (SYM && k > I) {
+        f64x2* tb = reinterpret_cast<f64x2*>(rows + (int64_t)ip[c >> 2] * BLK + (3 * (3 * kc + k) + I) * NEN + 4 * g);
+        tb[0] = f64x2{acc[0], acc[1]};
+        tb[1] = f64x2{acc[2], acc[3]};
+      }
+    }
+    if (g == 0) rows[(int64_t)ip[c >> 2] * BLK + 36 * NEN + 3 * (3 * kc + I) + k] = facc * s_c;
+  }
+}
+
+template <class Rule, bool SYM>
+__device__ __forceinline__ void elem_rows_mc64_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
+                                                    double* __restrict__ rows, int64_t blk) {
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, TH = rows64_threads<Rule>(), EB = rows64_elems<Rule>();
+  constexpr int RS = 3 * kSlot;
+  static_assert(Rule::MC == 4 && EB >= 1 && NQ % 2 == 0, "element rows of four-coefficient nodes");
+  constexpr size_t NOD = (size_t)EB * NEN * 6, REC = (size_t)EB * NQ * RS;
+  __shared__ __align__(16) double smem[NOD > REC ? NOD : REC];
+  __shared__ __align__(16) double fst[NEN == 16 ? 2 : EB * NEN * 9];  // force parts
+  __shared__ double dn[3 * NQ * NEN];  // unit-scaled parent gradients, dN_a(q)_m at NEN (NQ m + q) + a
+  const int tid = threadIdx.x;
+  const int64_t e0 = blk * EB;
+  const int ne = (int)(a.n_elem - e0 < EB ? a.n_elem - e0 : EB);
+  __shared__ RowsOut<Rule, EB> ro;
+  ro.fill(a, incpos, e0, ne);
+  gather_nodal<Rule>(a, e0, ne, smem);
+  for (int idx = tid; idx < NQ * NEN * 3; idx += TH) {
+    const int m = idx / (NQ * NEN), r = idx - m * NQ * NEN;
+    dn[idx] = Rule::dN_rt(r / NEN, r % NEN, m);
+  }
+  __syncthreads();
+  const bool act = tid < ne * NQ;
+  const int pl = act ? tid : 0;  // idle lanes evaluate point 0 and store nothing
+  const int el = pl / NQ, q = pl - el * NQ;
+  double Jinv[9], det, Hd[9], Fd[9];
+  tile_kinematics<Rule>(a, smem + 6 * NEN * el, nullptr, e0 + el, q, Jinv, det, Hd, Fd);
+  PointOut<double> o;
+  const unsigned fl = point_update<double, true>(a.mp, Hd, Fd, det * Rule::w_rt(q), a.alpha, a.beta, o);
+  if (act && fl) atomicOr(a.flags, fl);
+  HatOut<double> h;
+  to_parent<double, true>(o, Jinv, h);
+  sfor<0, 3>([&](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    __syncthreads();  // the nodal values, or the previous component's slots, are consumed
+    if (act) {
+      double* r = smem + pl * RS;
+      if constexpr (SYM && i > 0) {  // of the slots k < i the force part alone
+#pragma unroll
+        for (int k = 0; k < i; ++k) r[kSlot * k + 9] = h.P[3 * i + k];
+      }
+      sfor<(SYM ? i * kSlot / 2 : 0), RS / 2>([&](auto jc) __attribute__((always_inline)) {
+        constexpr int j = decltype(jc)::value;
+        f64x2 v;
+        v[0] = record_value<3 * kSlot * i + 2 * j, FuseOther>(h);
+        v[1] = record_value<3 * kSlot * i + 2 * j + 1, FuseOther>(h);
+        *reinterpret_cast<f64x2*>(r + 2 * j) = v;
+      });
+    }
+    __syncthreads();
+    if constexpr (NEN == 16) rows64_matrix<Rule, SYM, i>(ro, rows, ne, smem, dn);
+    else rows64_vector<Rule, i>(ro, rows, ne, smem, dn, fst);
+  });
+}
+
+template <class Rule, bool SYM>
+__global__ __launch_bounds__(rows64_threads<Rule>(), 2) void k_elem_rows_mc64(AsmArgs a,
+                                                                              const int32_t* __restrict__ incpos,
+                                                                              double* __restrict__ rows) {
+  elem_rows_mc64_tile<Rule, SYM>(a, incpos, rows, blockIdx.x);
+}
+
+template <class Rule>
+__global__ __launch_bounds__(rows64_threads<Rule>(), 2) void k_elem_rows_mc64_batch(BatchArgs b) {
+  const int64_t blk = blockIdx.x;
+  int lo = 0, hi = b.n_bodies - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (b.bodies[mid].rblock_off <= blk) lo = mid; else hi = mid - 1;
+  }
+  const BatchBody& B = b.bodies[lo];
+  const AsmArgs a = body_args(b, B, lo);
+  elem_rows_mc64_tile<Rule, false>(a, B.incpos, (double*)b.stage + B.blk_inc_off * rows_mc_block<Rule::NEN>(),
+                            blk - B.rblock_off);
+}
+
 // Pass 2 over the ANCF row blocks: a lane per (incidence, row r, component k)
 // loads its NEN entries (16-byte pieces) and its element's rank row (4 bytes,
 // element order), and adds them into the range's LDS segment at
 // row + 3 (4 rank_b + c_b) + k; every lane adds its force part to the row.
-template <class Rule, bool WANT_F, bool WANT_K, bool ACCUM>
+template <class Rule, typename R, bool WANT_F, bool WANT_K, bool ACCUM>
 __device__ __forceinline__ void gather_rows_mc(const GatherArgs& g, int32_t I0, int32_t I1, unsigned char* smem,
                                                int32_t* pre, int32_t* rowo) {
   constexpr int NEN = Rule::NEN, NPN = Rule::NPN, MC = 4, RPN = 3 * MC, TPI = 9 * MC;
@@ -1615,20 +1886,22 @@ __device__ __forceinline__ void gather_rows_mc(const GatherArgs& g, int32_t I0, 
   if constexpr (WANT_K) add_mass_term<MC>(g, I0, nn, lds, rowo);
   __syncthreads();
   const int ntask = pre[nn];
-  const float* blk = reinterpret_cast<const float*>(g.stage);
+  using V = typename Vec4<R>::type;
+  constexpr int PER = (int)(sizeof(V) / sizeof(R));
+  const R* blk = reinterpret_cast<const R*>(g.stage);
   for (int t = tid; t < ntask; t += blockDim.x) {
     const int jl = t / TPI, sl = t - TPI * jl, r = sl / 3, k = sl - 3 * r;
     const int64_t j = inc0 + jl;
     const int rl = RPN * incn[jl] + r;
-    const float* bj = blk + j * BLK;
+    const R* bj = blk + j * BLK;
     if constexpr (WANT_K) {
-      float val[NEN];
-      const f32x4* p = reinterpret_cast<const f32x4*>(bj + (3 * r + k) * NEN);
+      R val[NEN];
+      const V* p = reinterpret_cast<const V*>(bj + (3 * r + k) * NEN);
 #pragma unroll
-      for (int u = 0; u < NEN / 4; ++u) {
-        const f32x4 w = p[u];
+      for (int u = 0; u < NEN / PER; ++u) {
+        const V w = p[u];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) val[4 * u + x] = w[x];
+        for (int x = 0; x < PER; ++x) val[PER * u + x] = w[x];
       }
       const int32_t v = g.inc[j];
       const int64_t ea = (int64_t)(v >> 4) * NPN + (v & 15);
@@ -1650,16 +1923,16 @@ __device__ __forceinline__ void gather_rows_mc(const GatherArgs& g, int32_t I0, 
   }
 }
 
-template <class Rule, bool WANT_F, bool WANT_K, bool ACCUM>
+template <class Rule, typename R, bool WANT_F, bool WANT_K, bool ACCUM>
 __global__ __launch_bounds__(512) void k_gather_rows_mc(GatherArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t pre[kMaxRangeNodes + 1];
   __shared__ int32_t rowo[kMaxRangeNodes * 12];
   const int r = remap_tile(blockIdx.x, gridDim.x);
-  gather_rows_mc<Rule, WANT_F, WANT_K, ACCUM>(g, g.ranges[r], g.ranges[r + 1], smem, pre, rowo);
+  gather_rows_mc<Rule, R, WANT_F, WANT_K, ACCUM>(g, g.ranges[r], g.ranges[r + 1], smem, pre, rowo);
 }
 
-template <class Rule>
+template <class Rule, typename R>
 __global__ __launch_bounds__(512) void k_gather_rows_mc_batch(BatchArgs b) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t pre[kMaxRangeNodes + 1];
@@ -1672,11 +1945,11 @@ __global__ __launch_bounds__(512) void k_gather_rows_mc_batch(BatchArgs b) {
   g.inc = B.inc;
   g.row_off = B.row_off;
   g.rank = B.rank;
-  g.stage = (const float*)b.stage + B.blk_inc_off * rows_mc_block<Rule::NEN>();
+  g.stage = (const R*)b.stage + B.blk_inc_off * rows_mc_block<Rule::NEN>();
   g.f = b.f + B.dof_off;
   g.vals = b.vals + B.nnz_off;
   g.inc_cap = b.inc_cap;
-  gather_rows_mc<Rule, true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
+  gather_rows_mc<Rule, R, true, true, false>(g, br.I0, br.I1, smem, pre, rowo);
 }
 
 // ---------------------------------------------------------------------------
@@ -2002,9 +2275,18 @@ bool mc_mfma() {
 
 template <class Rule>
 int launch_rows_mc_points(const Mesh& m, const AsmArgs& a, hipStream_t s) {
-  constexpr int EB = rows_mc_elems<Rule>();
-  const int64_t blocks = (m.n_elem + EB - 1) / EB;
+  const int eb = m.precision == TLFEA_MIXED ? rows_mc_elems<Rule>() : rows64_elems<Rule>();
+  const int64_t blocks = (m.n_elem + eb - 1) / eb;
   if (blocks > INT32_MAX) return TLFEA_ERR_TOO_LARGE;
+  if (m.precision == TLFEA_FP64) {
+    const dim3 grid((unsigned)blocks), th(rows64_threads<Rule>());
+    if (blocks > 0 && sym_records(m) && Rule::NEN == 16)
+      hipLaunchKernelGGL((k_elem_rows_mc64<Rule, Rule::NEN == 16>), grid, th, 0, s, a, m.d_incpos, (double*)m.d_stage);
+    else if (blocks > 0)
+      hipLaunchKernelGGL((k_elem_rows_mc64<Rule, false>), grid, th, 0, s, a, m.d_incpos, (double*)m.d_stage);
+    TLFEA_HIP_CHECK(hipGetLastError());
+    return TLFEA_OK;
+  }
   // the shell's 16 x 16 slot tiles on the matrix cores (the beam's 8 x 8 slots
   // would fill half a tile: slower than its vector form, measured)
   constexpr bool MF = Rule::NEN == 16;
@@ -2026,7 +2308,7 @@ int launch_rows_mc_points(const Mesh& m, const AsmArgs& a, hipStream_t s) {
   return TLFEA_OK;
 }
 
-template <class Rule>
+template <class Rule, typename R>
 int launch_rows_mc_nodes(const Mesh& m, double* f, double* vals, bool accum, hipStream_t s, const GatherOptions& mt) {
   const bool want_f = f != nullptr, want_k = vals != nullptr;
   GatherArgs g{};
@@ -2048,8 +2330,8 @@ int launch_rows_mc_nodes(const Mesh& m, double* f, double* vals, bool accum, hip
   const dim3 grid((unsigned)m.n_ranges), blk(64 * m.tune.waves);
 #define TLFEA_GATHER(F, K, A)                                                   \
   do {                                                                          \
-    if (int rc = allow_lds(k_gather_rows_mc<Rule, F, K, A>, lds)) return rc;    \
-    hipLaunchKernelGGL((k_gather_rows_mc<Rule, F, K, A>), grid, blk, lds, s, g); \
+    if (int rc = allow_lds(k_gather_rows_mc<Rule, R, F, K, A>, lds)) return rc;    \
+    hipLaunchKernelGGL((k_gather_rows_mc<Rule, R, F, K, A>), grid, blk, lds, s, g); \
   } while (0)
   if (want_k && want_f) {
     if (accum) TLFEA_GATHER(true, true, true); else TLFEA_GATHER(true, true, false);
@@ -2061,6 +2343,14 @@ int launch_rows_mc_nodes(const Mesh& m, double* f, double* vals, bool accum, hip
 #undef TLFEA_GATHER
   TLFEA_HIP_CHECK(hipGetLastError());
   return TLFEA_OK;
+}
+
+// pass 2 over the row blocks (the two shell rules differ in pass 1 only)
+template <typename R>
+int launch_rows_nodes_prec(const Mesh& m, double* f, double* vals, bool accum, hipStream_t s, const GatherOptions& mt) {
+  if (m.elem_type == TLFEA_T10) return launch_rows_nodes<R>(m, f, vals, accum, s, mt);
+  if (m.elem_type == TLFEA_ANCF3243) return launch_rows_mc_nodes<RuleBeam, R>(m, f, vals, accum, s, mt);
+  return launch_rows_mc_nodes<RuleAncf<3, 3, 2>, R>(m, f, vals, accum, s, mt);
 }
 
 template <typename R>
@@ -2116,14 +2406,25 @@ static bool rows_on() {
 // (480,000: 2,014 / 1,795).
 constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
 
+// float64 element rows of the 3x3x2 shell: a workgroup's 21 slot tiles are a chain
+// that a small mesh waits for (65 elements 44 us with rows, 33 with records; 1,024
+// elements 53 / 43); with every CU busy the rows win (4,096 elements 86 / 92,
+// 10,000 damped 190 / 220, 65,536 1,003 / 1,166).  The beam and the 4x4x3 shell,
+// whose records are the larger (8.8 and 35 KB an element against 5.2 and 19.6),
+// take rows at every size (beam: 100 elements 22 / 25, 500,000 2,140 / 2,825;
+// 4x4x3: 64 elements 39 / 71, 10,000 257 / 434).
+constexpr int64_t kRows64MinShell = 3000;
+
 bool use_rows_batch(const Mesh& m, int64_t n_elem) {
   if (!rows_on() || !m.d_incpos || (m.elem_type == TLFEA_T10 && !m.d_rank_inc)) return false;
   if (m.precision == TLFEA_MIXED) return true;
-  return m.elem_type == TLFEA_T10 && n_elem >= kRows64MinElems && rows_addressable(m, sizeof(double));
+  if (m.elem_type == TLFEA_T10) return n_elem >= kRows64MinElems && rows_addressable(m, sizeof(double));
+  return m.elem_type == TLFEA_ANCF3243 || m.gl[0] != 3 || n_elem >= kRows64MinShell;
 }
 
 bool use_rows(const Mesh& m, bool want_k) {
-  return want_k && use_rows_batch(m, m.n_elem) && (m.precision == TLFEA_MIXED || !sym_records(m));
+  return want_k && use_rows_batch(m, m.n_elem) &&
+         (m.precision == TLFEA_MIXED || m.elem_type != TLFEA_T10 || !sym_records(m));
 }
 
 // The float64 point records of a tangent pass take the symmetric layout for
@@ -2154,10 +2455,14 @@ size_t row_block_bytes_for(int elem_type, int precision) {
   if (elem_type == TLFEA_T10) return kRowBlk * r;
   return (elem_type == TLFEA_ANCF3243 ? rows_mc_block<RuleBeam::NEN>() : rows_mc_block<16>()) * r;
 }
-int row_elems_for(int elem_type, int gl0, int64_t n_elem) {
+template <class Rule>
+static int mc_elems(int precision) {
+  return precision == TLFEA_MIXED ? rows_mc_elems<Rule>() : rows64_elems<Rule>();
+}
+int row_elems_for(int elem_type, int gl0, int precision, int64_t n_elem) {
   if (elem_type == TLFEA_T10) return tile_for(n_elem, kRowElems, 1);
-  if (elem_type == TLFEA_ANCF3243) return rows_mc_elems<RuleBeam>();
-  return gl0 == 3 ? rows_mc_elems<RuleAncf<3, 3, 2>>() : rows_mc_elems<RuleAncf<4, 4, 3>>();
+  if (elem_type == TLFEA_ANCF3243) return mc_elems<RuleBeam>(precision);
+  return gl0 == 3 ? mc_elems<RuleAncf<3, 3, 2>>(precision) : mc_elems<RuleAncf<4, 4, 3>>(precision);
 }
 
 size_t stage_record_bytes(int precision) {
@@ -2230,13 +2535,9 @@ int launch_nodes(const Mesh& m, double* f, double* vals, bool accum, hipStream_t
     int rc = f ? launch_zero(f, m.n_dof, s) : TLFEA_OK;
     return (rc || !vals) ? rc : launch_zero(vals, mt.row_off_u ? m.nnz_u : m.nnz, s);
   }
-  if (m.staged == 3 && m.elem_type == TLFEA_ANCF3243) return launch_rows_mc_nodes<RuleBeam>(m, f, vals, accum, s, mt);
-  if (m.staged == 3 && m.elem_type == TLFEA_ANCF3443)
-    return m.gl[0] == 3 ? launch_rows_mc_nodes<RuleAncf<3, 3, 2>>(m, f, vals, accum, s, mt)
-                        : launch_rows_mc_nodes<RuleAncf<4, 4, 3>>(m, f, vals, accum, s, mt);
   if (m.staged == 3)
-    return m.precision == TLFEA_MIXED ? launch_rows_nodes<float>(m, f, vals, accum, s, mt)
-                                      : launch_rows_nodes<double>(m, f, vals, accum, s, mt);
+    return m.precision == TLFEA_MIXED ? launch_rows_nodes_prec<float>(m, f, vals, accum, s, mt)
+                                      : launch_rows_nodes_prec<double>(m, f, vals, accum, s, mt);
   if (m.staged == 4) return vals ? TLFEA_ERR_INVALID : launch_force_sum(m, m.d_stage, f, accum, s);
   if (m.precision == TLFEA_MIXED) return launch_nodes_prec<float>(m, f, vals, accum, s, mt);
   return launch_nodes_prec<double>(m, f, vals, accum, s, mt);
@@ -2338,23 +2639,33 @@ int launch_rows_batch(const GatherTuning& tu, const BatchArgs& b, int n_ranges, 
   return TLFEA_OK;
 }
 
-template <class Rule>
+template <class Rule, typename R>
 int launch_rows_mc_batch(const GatherTuning& tu, const BatchArgs& b, int n_ranges, size_t lds, hipStream_t s) {
   constexpr bool MF = Rule::NEN == 16;  // the shell's slot tiles on the matrix cores
   if (b.n_rblocks > 0) {
-    if (mc_mfma())
-      hipLaunchKernelGGL((k_elem_rows_mc_batch<Rule, MF>), dim3((unsigned)b.n_rblocks), dim3(kRowsMcThreads), 0, s,
-                         b);
+    const dim3 grid((unsigned)b.n_rblocks);
+    if (sizeof(R) == 8)
+      hipLaunchKernelGGL(k_elem_rows_mc64_batch<Rule>, grid, dim3(rows64_threads<Rule>()), 0, s, b);
+    else if (mc_mfma())
+      hipLaunchKernelGGL((k_elem_rows_mc_batch<Rule, MF>), grid, dim3(kRowsMcThreads), 0, s, b);
     else
-      hipLaunchKernelGGL((k_elem_rows_mc_batch<Rule, false>), dim3((unsigned)b.n_rblocks), dim3(kRowsMcThreads), 0,
-                         s, b);
+      hipLaunchKernelGGL((k_elem_rows_mc_batch<Rule, false>), grid, dim3(kRowsMcThreads), 0, s, b);
   }
   TLFEA_HIP_CHECK(hipGetLastError());
   const size_t lds_all = lds + b.inc_cap;
-  if (int rc = allow_lds(k_gather_rows_mc_batch<Rule>, lds_all)) return rc;
-  hipLaunchKernelGGL(k_gather_rows_mc_batch<Rule>, dim3(n_ranges), dim3(64 * tu.waves), lds_all, s, b);
+  if (int rc = allow_lds(k_gather_rows_mc_batch<Rule, R>, lds_all)) return rc;
+  hipLaunchKernelGGL((k_gather_rows_mc_batch<Rule, R>), dim3(n_ranges), dim3(64 * tu.waves), lds_all, s, b);
   TLFEA_HIP_CHECK(hipGetLastError());
   return TLFEA_OK;
+}
+
+template <typename R>
+int launch_rows_batch_prec(int elem_type, int gl0, const GatherTuning& tu, const BatchArgs& b, int n_ranges, size_t lds,
+                           hipStream_t s) {
+  if (elem_type == TLFEA_T10) return launch_rows_batch<R>(tu, b, n_ranges, lds, s);
+  if (elem_type == TLFEA_ANCF3243) return launch_rows_mc_batch<RuleBeam, R>(tu, b, n_ranges, lds, s);
+  if (gl0 == 3) return launch_rows_mc_batch<RuleAncf<3, 3, 2>, R>(tu, b, n_ranges, lds, s);
+  return launch_rows_mc_batch<RuleAncf<4, 4, 3>, R>(tu, b, n_ranges, lds, s);
 }
 
 int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, const BatchArgs& b,
@@ -2378,14 +2689,10 @@ int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, 
     TLFEA_HIP_CHECK(hipGetLastError());
     return TLFEA_OK;
   }
-  if (b.rows && elem_type != TLFEA_T10) {
-    if (elem_type == TLFEA_ANCF3243) return launch_rows_mc_batch<RuleBeam>(tu, b, n_ranges, lds, s);
-    if (gl0 == 3) return launch_rows_mc_batch<RuleAncf<3, 3, 2>>(tu, b, n_ranges, lds, s);
-    return launch_rows_mc_batch<RuleAncf<4, 4, 3>>(tu, b, n_ranges, lds, s);
-  }
   const bool mixed = precision == TLFEA_MIXED;
   if (b.rows)
-    return mixed ? launch_rows_batch<float>(tu, b, n_ranges, lds, s) : launch_rows_batch<double>(tu, b, n_ranges, lds, s);
+    return mixed ? launch_rows_batch_prec<float>(elem_type, gl0, tu, b, n_ranges, lds, s)
+                 : launch_rows_batch_prec<double>(elem_type, gl0, tu, b, n_ranges, lds, s);
   if (elem_type == TLFEA_T10)
     return mixed ? launch_batch_rule<RuleT10, float>(tu, b, n_ranges, lds, s)
                  : launch_batch_rule<RuleT10, double>(tu, b, n_ranges, lds, s);

@@ -251,7 +251,7 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
   b->rows = 1;
   int64_t n_elem = 0;
   for (int i = 0; i < n_bodies; ++i) n_elem += meshes[i]->m.n_elem;
-  b->row_tile = tlfea::row_elems_for(b->elem_type, b->gl0, n_elem);
+  b->row_tile = tlfea::row_elems_for(b->elem_type, b->gl0, b->precision, n_elem);
   for (int i = 0; i < n_bodies; ++i)
     b->rows &= tlfea::use_rows_batch(meshes[i]->m, n_elem) ? 1 : 0;
   std::vector<BatchBody> bodies(n_bodies);

@@ -97,3 +97,30 @@ def test_t10_float64_rows_and_records():
     assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["fp64"] and rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["fp64"]
     for m in handles:
         m.close()
+
+
+# float64 element rows of the beam (five elements a wave) and of the shells (five
+# a workgroup of the 4x4x3 rule, seven of the 3x3x2 rule from 3,000 elements on)
+@pytest.mark.parametrize("damped", [True, False])
+@pytest.mark.parametrize("kind,n", [("beam", n) for n in (1, 4, 5, 6, 11)] + [("443", n) for n in (1, 4, 5, 6, 11)]
+                         + [("332", n) for n in (2999, 3000, 3001, 3003)])
+def test_float64_ancf_row_tiles(kind, n, damped):
+    print(f"[gpu] float64 ANCF rows {kind} {n} damped={damped}", flush=True)
+    mat = W.Material(W.SVK, (7e8, 0.33, 0.0), *((1e4, 7e3) if damped else ()))
+    if kind == "beam":
+        wl = W.beam_3243(12, 190 + n, "tile", material=mat)
+    else:
+        wl = W.shell_plate(4 if kind == "443" else 55, 190 + n, "tile", gl=tuple(int(c) for c in kind))
+        rng = np.random.default_rng(n)
+        wl = dataclasses.replace(wl, material=mat, qdot=rng.normal(0.0, 0.05, wl.q.shape))
+    wl = first_elements(wl, n)
+    m = make_mesh(wl, "fp64")
+    f_ref, v_ref = oracle.assemble(oracle.Mesh.of(wl.mesh), oracle.material_of(mat), wl.q, wl.qdot, 1e-3, 1.0)
+    f, v = m.assemble(cuda(wl.q), cuda(wl.qdot), 1e-3, 1.0)
+    f_only = torch.empty_like(f)
+    m.assemble_nodes(f_only)
+    torch.cuda.synchronize()
+    assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+    assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["fp64"]
+    assert rel_err(f_only.cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+    m.close()
