@@ -779,6 +779,9 @@ constexpr int kLptTile = 25;            // elements per item of the persistent b
 constexpr int kSymElems = 25;           // elements per pass-1 workgroup
 constexpr int kSymThreads = 128;        // 125 point lanes
 constexpr int kRecL = 92;               // LDS record stride in values (a 16-byte multiple; ANCF rows)
+constexpr int kRecSL = 68;              // of the shell's symmetric records: lanes store theirs to different banks (64: to the
+                                        // same ones, 65,536 shells 352 us, so 345; the beam and T10 keep 64, with which one
+                                        // workgroup more fits a CU: 500,000 beams 766 / 782, 480,000 T10 447 / 488)
 constexpr int kDnL = 20;                // LDS stride of a node's gradient row (16 used; 20 keeps the rows
                                         // of the ten nodes on different banks)
 constexpr int kStgL = 100;              // LDS stride of a staged row block (96 used; spreads the banks)
@@ -1265,7 +1268,7 @@ __global__ __launch_bounds__(512) void k_gather_rows_batch_lpt(BatchArgs b, cons
 // parts of a row are added in pass 2).
 constexpr int kRowsMcThreads = 128;
 #ifndef TLFEA_ROWS_MC_UNROLL
-#define TLFEA_ROWS_MC_UNROLL 2
+#define TLFEA_ROWS_MC_UNROLL 3
 #endif
 constexpr int kRowsMcUnroll = TLFEA_ROWS_MC_UNROLL;  // points contracted per step (divides 12, 18 and 48)
 template <class Rule>
@@ -1273,9 +1276,11 @@ constexpr int rows_mc_elems() { return kRowsMcThreads / Rule::NQ; }
 template <int NEN>
 constexpr int rows_mc_block() { return 36 * NEN + 36; }
 
-// What phase B needs of its elements from global memory, read before the first
-// store: loads and stores retire in one order, so a load between the stores of
-// two tasks would wait for the earlier ones to reach memory.
+// What phase B of the float64 form needs of its elements from global memory, read
+// before the first store: loads and stores retire in one order, so a load between
+// the stores of two tasks waits for the earlier ones to reach memory (pass 1 of
+// 65,536 shells 718 us, so 611; the float32 forms, with more waves to change to,
+// do not gain).
 template <class Rule, int EB>
 struct RowsOut {
   double sc[4 * EB];             // coefficient scales by kind
@@ -1286,34 +1291,59 @@ struct RowsOut {
   }
 };
 
+// floats between the records of two elements of the symmetric vector form, whose
+// lanes read the slots of up to three elements at once: 256-byte records alone would
+// put the same slot of all of them into the same banks
+constexpr int kElemPad = 12;
+
 // Phase B of the ANCF element rows for a symmetric tangent (undamped
 // materials): only the slots i <= k are contracted, a lane per task (element,
 // slot, coefficient a), coefficients fastest.  A task writes its NEN entries
 // K_e[(a, i), (b, k)] as in the full form and, for i < k, the same values as
 // the entries K_e[(b, k), (a, i)] of the blocks of the column coefficients'
 // nodes (the lanes of consecutive a write consecutive values), plus the force
-// parts of rows i and, for i < k, k.  Two thirds of the full form's tasks.
+// parts of rows i and, for i < k, k.  Two thirds of the full form's tasks.  A lane
+// takes two consecutive coefficients, which share the slot's values.  Bound by
+// vector issue (two thirds of the time: 3,190 instructions a wave, half of them
+// the points') and LDS.  Pass 1 of 500,000 beams 800 -> 749 us, 30,000 65 -> 54,
+// against one coefficient a lane with all gradients multiplied; blocks gathered in
+// LDS and stored whole took longer (970; non-temporal 773, but then pass 2 waits).
+// acc += sum over n of T_n dN_b,n(q) without the gradients that vanish at every
+// point; the order and the separate last addition are those of the full sum
+// ((t1 d1 + t0 d0) + t2 d2 with fused multiply-adds, then the accumulator), so the
+// results are the same bits.
+template <class Rule>
+__device__ __forceinline__ void add_column(float& acc, float t0, float t1, float t2, int q, int b) {
+#pragma clang fp contract(off)
+  float s = Rule::grad_nz(b, 1) ? fmaf(t0, Rule::dNf_rt(q, b, 0), t1 * Rule::dNf_rt(q, b, 1)) : t0 * Rule::dNf_rt(q, b, 0);
+  if (Rule::grad_nz(b, 2)) s = fmaf(t2, Rule::dNf_rt(q, b, 2), s);
+  acc = acc + s;
+}
+
 template <class Rule, int EB>
 __device__ __forceinline__ void rows_mc_sym_contract(const AsmArgs& a, const int32_t* __restrict__ incpos,
                                                      float* __restrict__ rows, int64_t e0, int ne, const float* rec,
                                                      const float* dn) {
-  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN;
+  constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, Z = 2, NT = NEN / Z * 6;
   constexpr int BLK = rows_mc_block<NEN>();
+  static_assert(Rule::grad_nz(0, 0) && Rule::grad_nz(1, 0) && Rule::grad_nz(2, 0) && Rule::grad_nz(3, 0), "first term");
   const int tid = threadIdx.x;
-  const int ntask = ne * NEN * 6;
-  for (int t0 = 0; t0 < EB * NEN * 6; t0 += kRowsMcThreads) {
+  const int ntask = ne * NT;
+  for (int t0 = 0; t0 < EB * NT; t0 += kRowsMcThreads) {
     const int t = t0 + tid;
     const bool on = t < ntask;
     const int tt = on ? t : ntask - 1;
-    const int le = tt / (NEN * 6), r6 = tt - le * NEN * 6, us = r6 / NEN, al = r6 - us * NEN;
+    const int le = tt / NT, r6 = tt - le * NT, us = r6 / (NEN / Z), al = Z * (r6 - us * (NEN / Z));
     const int i = us < 3 ? 0 : us < 5 ? 1 : 2, k = us < 3 ? us : us < 5 ? us - 2 : 2;
     const int so = kSlot * us, pt = 6 * kSlot + i + k - 1;  // the slot, Phat_ki (i < k)
-    float acc[NEN];
+    float acc[Z][NEN], facc[Z], ft[Z];
 #pragma unroll
-    for (int b = 0; b < NEN; ++b) acc[b] = 0.0f;
-    float facc = 0.0f, ft = 0.0f;
-    const float* recp = rec + le * NQ * kRecS;
-    static_assert(NQ % kRowsMcUnroll == 0, "point steps tile the rule");
+    for (int z = 0; z < Z; ++z) {
+#pragma unroll
+      for (int b = 0; b < NEN; ++b) acc[z][b] = 0.0f;
+      facc[z] = ft[z] = 0.0f;
+    }
+    const float* recp = rec + le * (NQ * kRecS + kElemPad);
 #pragma unroll 1
     for (int q0 = 0; q0 < NQ; q0 += kRowsMcUnroll) {
       sfor<0, kRowsMcUnroll>([&](auto uc) __attribute__((always_inline)) {
@@ -1326,41 +1356,53 @@ __device__ __forceinline__ void rows_mc_sym_contract(const AsmArgs& a, const int
           v[2 * x] = w[0];
           v[2 * x + 1] = w[1];
         }
+        const float pk = i < k ? r[pt] : 0.0f;
         const float* d = dn + 3 * (NEN * qq + al);
-        const float d0 = d[0], d1 = d[1], d2 = d[2];
-        const float t0n = v[0] * d0 + v[3] * d1 + v[6] * d2;
-        const float t1n = v[1] * d0 + v[4] * d1 + v[7] * d2;
-        const float t2n = v[2] * d0 + v[5] * d1 + v[8] * d2;
-        facc += v[9] * (k == 0 ? d0 : k == 1 ? d1 : d2);
-        if (i < k) ft += r[pt] * (i == 0 ? d0 : d1);
 #pragma unroll
-        for (int b = 0; b < NEN; ++b)
-          acc[b] += t0n * Rule::dNf_rt(qq, b, 0) + t1n * Rule::dNf_rt(qq, b, 1) + t2n * Rule::dNf_rt(qq, b, 2);
+        for (int z = 0; z < Z; ++z) {
+          const float d0 = d[3 * z], d1 = d[3 * z + 1], d2 = d[3 * z + 2];
+          const float t0n = sum3<false>(v[0], d0, v[3], d1, v[6], d2);
+          const float t1n = sum3<false>(v[1], d0, v[4], d1, v[7], d2);
+          const float t2n = sum3<false>(v[2], d0, v[5], d1, v[8], d2);
+          facc[z] += v[9] * (k == 0 ? d0 : k == 1 ? d1 : d2);
+          ft[z] += pk * (i == 0 ? d0 : d1);
+#pragma unroll
+          for (int b = 0; b < NEN; ++b) add_column<Rule>(acc[z][b], t0n, t1n, t2n, qq, b);
+        }
       });
     }
     if (on) {
       double sc[4];
       element_scales<Rule>(a, e0 + le, sc);
-      const float s_a = (float)sc[al & 3];
       const int32_t* ip = incpos + (e0 + le) * NPN;
-      const int c = al & 3, r = 3 * c + i;  // block row (kind, i)
-      float* blk = rows + (int64_t)ip[al >> 2] * BLK;
-      f32x4* outv = reinterpret_cast<f32x4*>(blk + (3 * r + k) * NEN);
+      float sa[Z];
 #pragma unroll
-      for (int u = 0; u < NEN / 4; ++u) {
-        f32x4 w;
+      for (int z = 0; z < Z; ++z) {
+        const int c = (al + z) & 3, r = 3 * c + i;  // block row (kind, i)
+        sa[z] = (float)(z == 0 ? ((al & 3) == 0 ? sc[0] : sc[2]) : ((al & 3) == 0 ? sc[1] : sc[3]));
+        float* blk = rows + (int64_t)ip[al >> 2] * BLK;
+        f32x4* outv = reinterpret_cast<f32x4*>(blk + (3 * r + k) * NEN);
 #pragma unroll
-        for (int x = 0; x < 4; ++x) w[x] = acc[4 * u + x] * s_a * (float)sc[x];  // b = 4 u + x: kind x
-        outv[u] = w;
+        for (int u = 0; u < NEN / 4; ++u) {
+          f32x4 w;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) w[x] = acc[z][4 * u + x] * sa[z] * (float)sc[x];  // b = 4 u + x: kind x
+          outv[u] = w;
+        }
+        blk[36 * NEN + 3 * r + k] = facc[z] * sa[z];
+        if (i < k) blk[36 * NEN + 3 * (3 * c + k) + i] = ft[z] * sa[z];
       }
-      blk[36 * NEN + 3 * r + k] = facc * s_a;
       if (i < k) {
-        blk[36 * NEN + 3 * (3 * c + k) + i] = ft * s_a;
 #pragma unroll
         for (int nb = 0; nb < NPN; ++nb) {
           float* ob = rows + (int64_t)ip[nb] * BLK;
 #pragma unroll
-          for (int x = 0; x < 4; ++x) ob[(3 * (3 * x + k) + i) * NEN + al] = acc[4 * nb + x] * s_a * (float)sc[x];
+          for (int x = 0; x < 4; ++x) {
+            f32x2 w;
+#pragma unroll
+            for (int z = 0; z < Z; ++z) w[z] = acc[z][4 * nb + x] * sa[z] * (float)sc[x];
+            *reinterpret_cast<f32x2*>(ob + (3 * (3 * x + k) + i) * NEN + al) = w;
+          }
         }
       }
     }
@@ -1397,7 +1439,7 @@ __device__ __forceinline__ void rows_mc_mfma_contract(const AsmArgs& a, const in
                                                       const float* dn) {
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, BLK = rows_mc_block<NEN>();
   static_assert(NEN == 16, "one 16 x 16 tile per slot");
-  constexpr int RS = SYM ? kRecS : kRecL;
+  constexpr int RS = SYM ? kRecSL : kRecL;
   constexpr int KK = 3 * NQ, NSTEP = (KK + 3) / 4, NSL = SYM ? 6 : 9, NW = kRowsMcThreads / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, c16 = lane & 15;
@@ -1472,9 +1514,10 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
                                                   float* __restrict__ rows, int64_t blk) {
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, NPN = Rule::NPN, EB = rows_mc_elems<Rule>();
   constexpr int BLK = rows_mc_block<NEN>();
-  constexpr int RS = SYM ? kRecS : kRecL;  // LDS record stride (symmetric layout for undamped materials)
+  constexpr int RS = SYM ? (MF ? kRecSL : kRecS) : kRecL;  // LDS record stride (symmetric layout for undamped materials)
   static_assert(Rule::MC == 4 && NEN % 4 == 0 && EB >= 1, "element rows of four-coefficient nodes");
-  constexpr size_t NOD = (size_t)EB * NEN * 6 * sizeof(double), REC = (size_t)EB * NQ * RS * sizeof(float);
+  constexpr int PAD = SYM && !MF ? kElemPad : 0;
+  constexpr size_t NOD = (size_t)EB * NEN * 6 * sizeof(double), REC = (size_t)EB * (NQ * RS + PAD) * sizeof(float);
   __shared__ __align__(16) unsigned char smem[NOD > REC ? NOD : REC];
   __shared__ float dn[NQ * NEN * 3];  // unit-scaled parent gradients, dN_a(q)_m at 3 (NEN q + a) + m
   const int tid = threadIdx.x;
@@ -1503,8 +1546,8 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
   to_parent<float, true, FO>(o, Jinv, h);
   float* rec = reinterpret_cast<float*>(smem);
   if (act) {
-    float* r = rec + pl * RS;
-    sfor<0, RS / 4>([&](auto jc) __attribute__((always_inline)) {
+    float* r = rec + pl * RS + el * PAD;
+    sfor<0, (SYM ? kRecS : kRecL) / 4>([&](auto jc) __attribute__((always_inline)) {
       constexpr int j = decltype(jc)::value;
       f32x4 v;
       sfor<0, 4>([&](auto xc) __attribute__((always_inline)) {

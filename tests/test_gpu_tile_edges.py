@@ -124,3 +124,23 @@ def test_float64_ancf_row_tiles(kind, n, damped):
     assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["fp64"]
     assert rel_err(f_only.cpu().numpy(), f_ref)[0] <= TOL["fp64"]
     m.close()
+
+
+# mixed element rows of undamped ANCF meshes: ten beams a workgroup, two
+# coefficients a lane; seven and two shells
+@pytest.mark.parametrize("kind,n", [("beam", n) for n in (1, 2, 9, 10, 11, 21)] + [("332", n) for n in (1, 6, 7, 8)]
+                         + [("443", n) for n in (1, 2, 3)])
+def test_mixed_ancf_row_tiles(kind, n):
+    print(f"[gpu] mixed ANCF rows {kind} {n}", flush=True)
+    if kind == "beam":
+        wl = W.beam_3243(22, 230 + n, "tile")
+    else:
+        wl = W.shell_plate(3, 230 + n, "tile", gl=tuple(int(c) for c in kind))
+    wl = first_elements(wl, n)
+    m = make_mesh(wl, "mixed")
+    f_ref, v_ref = oracle.assemble(oracle.Mesh.of(wl.mesh), oracle.material_of(wl.material), wl.q, wl.qdot, 1e-3, 1.0)
+    f, v = m.assemble(cuda(wl.q), cuda(wl.qdot), 1e-3, 1.0)
+    torch.cuda.synchronize()
+    assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
+    assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
+    m.close()
