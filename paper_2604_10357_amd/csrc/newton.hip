@@ -165,12 +165,9 @@ __global__ void k_mass_values(const int32_t* adj_off, const int32_t* row_off, co
     }
 }
 
-// g = M (v - v_prev) / h + f_int - f_ext: LANES lanes per pattern node split
-// its mass row (consecutive entries: coalesced loads), UNR entries per lane
-// and step in flight, and sum their parts with a fixed butterfly of shuffles;
-// the group's lanes then write the node's 3 MC rows of g, lane j taking rows
-// j, j + LANES, ...  T10 nodes have about 28 neighbours (8 lanes), ANCF nodes
-// 3 (beam) or 9 (shell) (4 lanes).
+// g = M (v - v_prev) / h + f_int - f_ext, a group of lanes per pattern node: T10
+// nodes have about 28 neighbours (8 lanes), ANCF nodes 3 (beam) or 9 (shell) with
+// 4 x 4 mass blocks (4 lanes).
 #ifndef TLFEA_GRAD_UNROLL
 #define TLFEA_GRAD_UNROLL 2
 #endif
@@ -181,18 +178,20 @@ __global__ void k_vdiff(const double* v, const double* vp, int64_t n, double* dv
   if (i < n) dv[i] = v[i] - vp[i];
 }
 
-// T10 (about 28 neighbours per node) gathers v - v_prev formed once per DOF
-// (dv, vp null); ANCF (3 or 9) forms the difference at each gather.
+// T10: the lanes split the mass row (consecutive entries: coalesced loads), UNR
+// entries per lane and step in flight, and sum their parts with a fixed butterfly
+// of shuffles; v - v_prev is formed once per DOF before.
 // SUM: f_int is not given but summed here from the element force blocks of the
-// node's incidences (3 MC values each, node-sorted), spread over the group's
-// lanes, reduced beside the mass row and written to fint.
-template <int MC, bool SUM, typename R>
-__global__ __launch_bounds__(256) void k_gradient(const int32_t* adj_off, const int32_t* adj, const double* mass,
-                                                  int64_t n_nodes, const double* dv, const double* vp,
-                                                  double* fint, const double* fext, double inv_h, double* g,
-                                                  const int32_t* __restrict__ inc_off, const R* __restrict__ blocks) {
-  constexpr int NR = 3 * MC;  // rows per node: (coefficient k, component d) at 3 k + d
-  constexpr int LANES = grad_lanes<MC>(), UNR = TLFEA_GRAD_UNROLL;
+// node's incidences (node-sorted), spread over the group's lanes, reduced beside
+// the mass row and written to fint.
+template <bool SUM, typename R>
+__global__ __launch_bounds__(256) void k_gradient_t10(const int32_t* adj_off, const int32_t* adj, const double* mass,
+                                                      int64_t n_nodes, const double* dv, double* fint,
+                                                      const double* fext, double inv_h, double* g,
+                                                      const int32_t* __restrict__ inc_off,
+                                                      const R* __restrict__ blocks) {
+  constexpr int NR = 3;
+  constexpr int LANES = grad_lanes<1>(), UNR = TLFEA_GRAD_UNROLL;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t I = t / LANES;
   const int sub = (int)(t % LANES);
@@ -208,24 +207,10 @@ __global__ __launch_bounds__(256) void k_gradient(const int32_t* adj_off, const 
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         if (J[u] < 0) continue;
-        const double* mx = mass + (int64_t)MC * MC * (x0 + u * LANES);
+        const double m = mass[x0 + u * LANES];
+        const int64_t c = 3 * J[u];
 #pragma unroll
-        for (int l = 0; l < MC; ++l) {
-          const int64_t c = 3 * (MC * J[u] + l);
-          double d0 = dv[c], d1 = dv[c + 1], d2 = dv[c + 2];
-          if constexpr (MC != 1) {
-            d0 -= vp[c];
-            d1 -= vp[c + 1];
-            d2 -= vp[c + 2];
-          }
-#pragma unroll
-          for (int k = 0; k < MC; ++k) {
-            const double m = mx[MC * k + l];
-            s[3 * k] += m * d0;
-            s[3 * k + 1] += m * d1;
-            s[3 * k + 2] += m * d2;
-          }
-        }
+        for (int d = 0; d < 3; ++d) s[d] += m * dv[c + d];
       }
     }
   }
@@ -268,13 +253,91 @@ __global__ __launch_bounds__(256) void k_gradient(const int32_t* adj_off, const 
   }
 }
 
+// ANCF: the group's four lanes are the column kinds l of the
+// neighbours' coefficients in the mass row, so that a load of a group is
+// consecutive (32 bytes of a mass block, 96 of a velocity; a lane per neighbour
+// reads 8 bytes from each of 64 lines: 500,001 beam nodes 150 us, so 91, of which
+// the 430 MB it has to move take 82).
+// After the row sums lane k keeps coefficient k, whose three rows it reads, sums
+// (SUM) and writes.
+template <int N>
+__device__ __forceinline__ void fold(double* s, int lane_bit, bool upper) {
+  // s[0 .. 2 N): the lane keeps the half that its bit names and adds its partner's
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const double send = upper ? s[j] : s[N + j], keep = upper ? s[N + j] : s[j];
+    s[j] = keep + __shfl_xor(send, lane_bit, 4);
+  }
+}
+
+template <bool SUM, typename R>
+__global__ __launch_bounds__(256) void k_gradient_ancf(const int32_t* adj_off, const int32_t* adj, const double* mass,
+                                                       int64_t n_nodes, const double* v, const double* vp,
+                                                       double* fint, const double* fext, double inv_h, double* g,
+                                                       const int32_t* __restrict__ inc_off,
+                                                       const R* __restrict__ blocks) {
+  constexpr int UNR = 3;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t I = t >> 2;
+  const int l = (int)(t & 3);
+  double s[12];
+#pragma unroll
+  for (int j = 0; j < 12; ++j) s[j] = 0.0;
+  if (I < n_nodes) {
+    const int32_t x1 = adj_off[I + 1];
+    for (int32_t x0 = adj_off[I]; x0 < x1; x0 += UNR) {
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int32_t x = x0 + u;
+        if (x >= x1) continue;
+        const int64_t c = 3 * (4 * (int64_t)adj[x] + l);
+        const double* mx = mass + 16 * (int64_t)x + l;
+        const double d0 = v[c] - vp[c], d1 = v[c + 1] - vp[c + 1], d2 = v[c + 2] - vp[c + 2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const double m = mx[4 * k];
+          s[3 * k] += m * d0;
+          s[3 * k + 1] += m * d1;
+          s[3 * k + 2] += m * d2;
+        }
+      }
+    }
+  }
+  fold<6>(s, 2, (l & 2) != 0);  // all lanes take part; groups never straddle a wave
+  fold<3>(s, 1, (l & 1) != 0);
+  if (I >= n_nodes) return;
+  const int64_t r = 12 * I + 3 * l;
+  double f[3];
+  if constexpr (SUM) {
+    f[0] = f[1] = f[2] = 0.0;
+    const int32_t x1 = inc_off[I + 1];
+    for (int32_t x = inc_off[I]; x < x1; ++x) {
+      const R* b = blocks + 12 * (int64_t)x + 3 * l;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) f[d] += (double)b[d];
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) fint[r + d] = f[d];
+  } else {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) f[d] = fint[r + d];
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) g[r + d] = s[d] * inv_h + f[d] - (fext ? fext[r + d] : 0.0);
+}
+
 int blocks_of(int64_t n, int b) { return (int)((n + b - 1) / b); }
 
 template <int MC, bool SUM, typename R>
 void launch_gradient(const Mesh& m, const double* dv, const double* vp, double* fint, const double* fext,
                      double h, double* g, const R* blocks, hipStream_t s) {
-  hipLaunchKernelGGL((k_gradient<MC, SUM, R>), dim3(blocks_of(m.n_pnodes * grad_lanes<MC>(), 256)), dim3(256), 0, s,
-                     m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes, dv, vp, fint, fext, 1.0 / h, g, m.d_inc_off, blocks);
+  const dim3 grid(blocks_of(m.n_pnodes * grad_lanes<MC>(), 256));
+  if constexpr (MC == 1)
+    hipLaunchKernelGGL((k_gradient_t10<SUM, R>), grid, dim3(256), 0, s, m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes, dv,
+                       fint, fext, 1.0 / h, g, m.d_inc_off, blocks);
+  else
+    hipLaunchKernelGGL((k_gradient_ancf<SUM, R>), grid, dim3(256), 0, s, m.d_adj_off, m.d_adj, m.d_mass, m.n_pnodes,
+                       dv, vp, fint, fext, 1.0 / h, g, m.d_inc_off, blocks);
 }
 
 }  // namespace

@@ -144,3 +144,21 @@ def test_mixed_ancf_row_tiles(kind, n):
     assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
     assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
     m.close()
+
+
+# ANCF gradient: four lanes a node (64 nodes a workgroup), three neighbours a step;
+# shell nodes have 4, 6 or 9
+@pytest.mark.parametrize("kind,n", [("beam", 1), ("beam", 62), ("beam", 63), ("beam", 64), ("332", 1), ("332", 9)])
+def test_ancf_gradient_nodes(kind, n):
+    print(f"[gpu] ANCF gradient {kind} {n}", flush=True)
+    wl = W.beam_3243(n, 260, "grad") if kind == "beam" else W.shell_plate(n, 261, "grad")
+    m = make_mesh(wl, "fp64")
+    m.build_mass(1200.0)
+    om = oracle.Mesh.of(wl.mesh)
+    pat = oracle.csr_pattern(om)
+    rng = np.random.default_rng(262)
+    v, v_prev, f, f_ext = (rng.normal(0, 1.0, wl.mesh.n_dof) for _ in range(4))
+    g_ref = oracle.gradient(pat, oracle.mass_csr(om, 1200.0, pat), v, v_prev, f, f_ext, 1e-3)
+    g = m.newton_gradient(cuda(v), cuda(v_prev), cuda(f), cuda(f_ext), 1e-3)
+    assert rel_err(g.cpu().numpy(), g_ref)[0] <= 1e-12
+    m.close()
