@@ -30,6 +30,9 @@
 //     stores.  f_int comes out of the same pass from Phat.
 //   Workgroups are remapped so each XCD walks a contiguous range of elements /
 //   nodes, keeping the records a range reads in its own L2.
+//
+// Most tangents contract the element's points in pass 1 instead, into one block
+// per (element, node) that pass 2 reads once (the element rows below).
 #include <cstdlib>
 #include <map>
 #include <mutex>
@@ -1256,7 +1259,7 @@ __global__ __launch_bounds__(512) void k_gather_rows_batch_lpt(BatchArgs b, cons
 }
 
 // ---------------------------------------------------------------------------
-// element rows for ANCF (four coefficient vectors per node; float32 tangent)
+// element rows for ANCF (four coefficient vectors per node)
 // ---------------------------------------------------------------------------
 // The same split as for T10, for the shell and the beam: pass 1 contracts an
 // element's points itself and leaves one block per (element, node) incidence
@@ -2658,14 +2661,6 @@ __global__ void k_params(int kind, const double* __restrict__ p, double* __restr
 
 int launch_params(const Mesh& m, const double* d_params, hipStream_t s) {
   hipLaunchKernelGGL(k_params, dim3(1), dim3(64), 0, s, m.material, d_params, m.d_mp);
-  TLFEA_HIP_CHECK(hipGetLastError());
-  return TLFEA_OK;
-}
-
-int launch_block_sum(const Mesh& m, const double* blk, double* out, hipStream_t s) {
-  if (m.n_dof > 0)
-    hipLaunchKernelGGL(k_force_sum<double>, dim3(grid_of(m.n_dof, 256)), dim3(256), 0, s, m.d_inc_off, blk, m.n_dof,
-                       3 * m.mc, false, out);
   TLFEA_HIP_CHECK(hipGetLastError());
   return TLFEA_OK;
 }

@@ -185,9 +185,8 @@ __global__ __launch_bounds__(kVjpThreads, (Rule::MC == 1 ? 2 : 1)) void k_vjp_el
 // lane t of kFinGroups * 5 sums every kFinGroups * 5-th value from t on (one
 // parameter each, four loads in flight), then a tree over the groups.
 constexpr int kFinGroups = 204, kFinThreads = 1024, kFinTree = 256;
-__global__ __launch_bounds__(kFinThreads) void k_vjp_finalize(const double* __restrict__ gpart, int64_t n_blocks,
-                                                              int kind, double E, double nu,
-                                                              const double* __restrict__ d_params, double* gparam) {
+__device__ __forceinline__ void vjp_finalize(const double* __restrict__ gpart, int64_t n_blocks, int kind, double E,
+                                             double nu, const double* __restrict__ d_params, double* gparam) {
   constexpr int S = 5 * kFinGroups;
   __shared__ double red[kFinTree][5];
   const int t = threadIdx.x;
@@ -230,6 +229,51 @@ __global__ __launch_bounds__(kFinThreads) void k_vjp_finalize(const double* __re
   }
   gparam[3] = g[3];
   gparam[4] = g[4];
+}
+
+// What follows the element kernel, in one launch: workgroup 0 finalizes the
+// parameters' gradient (its chain of loads runs beside the others), then n_sum
+// workgroups sum the q blocks of the nodes' incidences, then as many the qdot
+// blocks; a gradient that is not asked for has no workgroups.  Forward and
+// backward of 112,398 elements with all three: 152 us with three launches, 144.
+struct VjpTail {
+  const int32_t* inc_off;
+  const double *bq, *bqd, *gpart, *d_params;
+  double *gq, *gqd, *gparam;
+  int64_t n_rows, n_blocks;
+  double E, nu;
+  int n_sum, kind;
+};
+template <int RPN>
+__global__ __launch_bounds__(kFinThreads) void k_vjp_tail(VjpTail t) {
+  int b = (int)blockIdx.x;
+  if (t.gparam) {
+    if (b == 0) {
+      vjp_finalize(t.gpart, t.n_blocks, t.kind, t.E, t.nu, t.d_params, t.gparam);
+      return;
+    }
+    --b;
+  }
+  const bool second = !t.gq || b >= t.n_sum;
+  if (t.gq && second) b -= t.n_sum;
+  const double* __restrict__ blocks = second ? t.bqd : t.bq;
+  const int64_t r = (int64_t)b * kFinThreads + threadIdx.x;
+  if (r >= t.n_rows) return;
+  const int64_t I = r / RPN;
+  const int j = (int)(r - I * RPN);
+  double s = 0.0;  // four loads in flight, summed in incidence order
+  int32_t x = t.inc_off[I];
+  const int32_t x1 = t.inc_off[I + 1];
+  for (; x + 4 <= x1; x += 4) {
+    const double* v = blocks + (int64_t)x * RPN + j;
+    const double v0 = v[0], v1 = v[RPN], v2 = v[2 * RPN], v3 = v[3 * RPN];
+    s += v0;
+    s += v1;
+    s += v2;
+    s += v3;
+  }
+  for (; x < x1; ++x) s += blocks[(int64_t)x * RPN + j];
+  (second ? t.gqd : t.gq)[r] = s;
 }
 
 template <class Rule>
@@ -284,11 +328,12 @@ int launch_vjp(Mesh& m, const double* q, const double* qdot, const double* w, do
   else if (m.gl[0] == 3) rc = launch_vjp_elem<RuleAncf<3, 3, 2>>(a, w, m.d_incpos, bq, bqd, gpart, s);
   else rc = launch_vjp_elem<RuleAncf<4, 4, 3>>(a, w, m.d_incpos, bq, bqd, gpart, s);
   if (rc) return rc;
-  if (gq && (rc = launch_block_sum(m, bq, gq, s))) return rc;
-  if (gqdot && (rc = launch_block_sum(m, bqd, gqdot, s))) return rc;
-  if (gparam) {
-    hipLaunchKernelGGL(k_vjp_finalize, dim3(1), dim3(kFinThreads), 0, s, gpart, blocks, m.material, m.params[0],
-                       m.params[1], d_params, gparam);
+  VjpTail t{m.d_inc_off, bq, bqd, gpart, d_params, gq, gqdot, gparam, m.n_dof, blocks, m.params[0], m.params[1],
+            (int)((m.n_dof + kFinThreads - 1) / kFinThreads), m.material};
+  const unsigned grid = (gparam ? 1u : 0u) + (unsigned)t.n_sum * ((gq ? 1u : 0u) + (gqdot ? 1u : 0u));
+  if (grid > 0) {
+    if (m.mc == 1) hipLaunchKernelGGL(k_vjp_tail<3>, dim3(grid), dim3(kFinThreads), 0, s, t);
+    else hipLaunchKernelGGL(k_vjp_tail<12>, dim3(grid), dim3(kFinThreads), 0, s, t);
     TLFEA_HIP_CHECK(hipGetLastError());
   }
   return TLFEA_OK;

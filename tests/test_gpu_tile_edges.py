@@ -162,3 +162,24 @@ def test_ancf_gradient_nodes(kind, n):
     g = m.newton_gradient(cuda(v), cuda(v_prev), cuda(f), cuda(f_ext), 1e-3)
     assert rel_err(g.cpu().numpy(), g_ref)[0] <= 1e-12
     m.close()
+
+
+# the backward product's sums: 1,024 rows a workgroup, one more workgroup for the
+# parameters; every subset of the three gradients
+@pytest.mark.parametrize("want", [(True, False, False), (False, True, False), (False, False, True),
+                                  (True, True, False), (True, False, True), (False, True, True)])
+@pytest.mark.parametrize("kind", ["t10", "beam"])
+def test_vjp_subsets(kind, want):
+    print(f"[gpu] vjp subset {kind} {want}", flush=True)
+    kv = W.Material(W.SVK, (7e8, 0.33, 0.0), 1e4, 7e3)
+    wl = W.t10_beam(6, 3, 2, 270, "sub", material=kv) if kind == "t10" else W.beam_3243(85, 271, "sub", material=kv)
+    m = make_mesh(wl, "fp64")
+    refs = oracle.vjp(oracle.Mesh.of(wl.mesh), oracle.material_of(kv), wl.q, wl.qdot, wl.w)
+    got = m.vjp(cuda(wl.q), cuda(wl.qdot), cuda(wl.w), *want)
+    for x, ref, on in zip(got[:2], refs, want):
+        assert (x is not None) == on
+        if on:
+            assert rel_err(x.cpu().numpy(), ref)[0] <= TOL["fp64"]
+    if want[2]:
+        assert np.abs(got[2].cpu().numpy() - refs[2]).max() <= 1e-12 * np.abs(refs[2]).max()
+    m.close()
