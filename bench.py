@@ -45,9 +45,9 @@ def contraction_flop(wl):
 # committed counter reports: file and the two kernels of the mixed call, per workload
 TRAFFIC = {
     "t10_beam": ("hbm_traffic_t10_beam_200x20x20_mixed.json",
-                 ("k_elem_rows<RuleT10, false>", "k_gather_rows<true, true, false>")),
+                 ("k_elem_rows<RuleT10, float>", "k_gather_rows<float, true, true, false>")),
     "ancf_beam": ("hbm_traffic_ancf3243_chain_500000_mixed.json",
-                  ("k_elem_rows_mc<RuleBeam, true, false>", "k_gather_rows_mc<RuleBeam, true, true, false>")),
+                  ("k_elem_rows_mc<RuleBeam, true, false>", "k_gather_rows_mc<RuleBeam, float, true, true, false>")),
 }
 
 
@@ -289,7 +289,10 @@ def bench_mesh(args, torch, wl, wname):
     traffic = measured_traffic(wname, args.precision, tuning["gather_shape"])
     kname = {1: "T10", 2: "ANCF3443", 3: "ANCF3243"}[wl.mesh.elem_type]
     # the tangent in mixed precision takes the element-row kernels
-    rows_path = args.precision == "mixed" and os.environ.get("TLFEA_ELEMENT_ROWS") != "0"
+    mixed = args.precision == "mixed"
+    damped = bool(wl.material.kv_eta or wl.material.kv_lambda)
+    rows_path = os.environ.get("TLFEA_ELEMENT_ROWS") != "0" and (
+        mixed or (damped and n_el >= 49152 if kname == "T10" else n_el >= 3000))
     mat = "mooney_rivlin" if wl.material.kind == 2 else "svk"
     if wl.material.kv_eta or wl.material.kv_lambda:
         mat += "+kelvin_voigt"
@@ -311,15 +314,15 @@ def bench_mesh(args, torch, wl, wname):
         "tuning": tuning,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": (f"k_elem_rows{'' if kname == 'T10' else '_mc'} + k_gather_rows"
+                     "kernel": (f"k_elem_rows{'' if kname == 'T10' else '_mc' if mixed else '_mc64'} + k_gather_rows"
                                 f"{'' if kname == 'T10' else '_mc'} ({kname}, f + K)" if rows_path else
                                 f"k_stage_tile + k_gather ({kname}, f + K)"), "kernel_ms": ms,
                      "pass1_stage_ms": ms1, "pass2_gather_ms": ms2, "algorithmic_bytes": B,
                      "algorithmic_bytes_layout": B_layout,
                      "frac_layout": B_layout / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
         # the same call against the vector arithmetic roofline (contraction FLOPs only)
-        # the shell's mixed contraction runs on the matrix cores (FP32 MFMA, the same 157.3 peak)
-        "valu": {"units": ("matrix cores (fp32 MFMA 16x16x4)" if kname == "ANCF3443" and rows_path
+        # the shell's contraction runs on the matrix cores (the same peaks as the vector units)
+        "valu": {"units": (f"matrix cores ({'fp32' if mixed else 'fp64'} MFMA 16x16x4)" if kname == "ANCF3443" and rows_path
                            else "vector ALUs"),
                  "flop_per_element": contraction_flop(wl),
                  "achieved_TFLOPs": contraction_flop(wl) * n_el / (ms * 1e-3) / 1e12,
@@ -511,7 +514,7 @@ def bench_batched(args, torch):
         fp64 = {"ms_per_step": ms64, "value": n_el / (ms64 * 1e-3), "speedup_mixed_over_fp64": ms64 / ms,
                 "mixed_vs_fp64": {"f": float(np.abs(f_mx - f64).max() / np.abs(f64).max()),
                                   "K": float(np.abs(v_mx - v64).max() / np.abs(v64).max())},
-                "kernel": "k_stage_batch + k_gather_batch (one graph)"}
+                "kernel": "k_elem_rows_batch + k_gather_rows_batch (one graph)"}
         b64.close()
         for m in meshes64:
             m.close()
@@ -529,7 +532,7 @@ def bench_batched(args, torch):
                      "kernel": (("k_elem_rows_batch_lpt + k_gather_rows_batch_lpt (persistent, one graph)"
                                  if tuning["schedule"]["persistent"] else
                                  "k_elem_rows_batch + k_gather_rows_batch (one graph)") if args.precision == "mixed"
-                                else "k_stage_batch + k_gather_batch (one graph)"), "kernel_ms": ms,
+                                else "k_elem_rows_batch + k_gather_rows_batch (one graph)"), "kernel_ms": ms,
                      "algorithmic_bytes": B},
         "per_body_loop": {"ms_per_step": ms_loop, "value": n_el / (ms_loop * 1e-3),
                           "speedup_batched_over_loop": ms_loop / ms},
