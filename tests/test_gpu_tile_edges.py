@@ -183,3 +183,32 @@ def test_vjp_subsets(kind, want):
     if want[2]:
         assert np.abs(got[2].cpu().numpy() - refs[2]).max() <= 1e-12 * np.abs(refs[2]).max()
     m.close()
+
+
+# float64 ANCF batches: bodies of less than a tile, more than one, a large one (the
+# 3x3x2 shells' line of 3,000 elements counts the batch's total); materials differ
+@pytest.mark.parametrize("kind,sizes", [("beam", (1, 11, 5)), ("443", (1, 3, 2)), ("332", (2, 55, 1))])
+def test_float64_ancf_batch(kind, sizes):
+    print(f"[gpu] float64 ANCF batch {kind}", flush=True)
+    wls = []
+    for i, n in enumerate(sizes):
+        mat = W.Material(W.SVK, (7e8, 0.33, 0.0), *((1e4, 7e3) if i % 2 else ()))
+        if kind == "beam":
+            wl = W.beam_3243(n, 280 + i, "batch", material=mat)
+        else:
+            wl = W.shell_plate(n, 280 + i, "batch", gl=tuple(int(c) for c in kind))
+            qdot = np.random.default_rng(i).normal(0.0, 0.05, wl.q.shape)
+            wl = dataclasses.replace(wl, material=mat, qdot=qdot)
+        wls.append(wl)
+    handles = [make_mesh(wl, "fp64") for wl in wls]
+    b = TLBatch(handles)
+    q, qd = (cuda(np.concatenate([getattr(wl, k) for wl in wls])) for k in ("q", "qdot"))
+    f, v = b.assemble(q, qd, torch.full((len(wls),), 1e-3, dtype=torch.float64, device="cuda"))
+    torch.cuda.synchronize()
+    for i, wl in enumerate(wls):
+        f_ref, v_ref = oracle.assemble(oracle.Mesh.of(wl.mesh), oracle.material_of(wl.material), wl.q, wl.qdot, 1e-3, 1.0)
+        assert rel_err(f[b.dof_off[i]:b.dof_off[i + 1]].cpu().numpy(), f_ref)[0] <= TOL["fp64"]
+        assert rel_err(v[b.nnz_off[i]:b.nnz_off[i + 1]].cpu().numpy(), v_ref)[0] <= TOL["fp64"]
+    b.close()
+    for m in handles:
+        m.close()
