@@ -248,6 +248,11 @@ int tlfea_assemble_upper(tlfea_mesh_t mesh, const double* d_q, const double* d_q
  *     parent coordinates with the quadrature volume folded in; without the
  *     tangent (want_tangent = 0), each element's force, one block per
  *     incidence.  Allocates the buffer when it is too small (synchronising).
+ *     In float64 the per-element rows of a large mesh may need more than the
+ *     per-point form; a buffer that already holds the latter (the mesh's tangent
+ *     ran undamped, or in mixed precision) is kept and the per-point form taken,
+ *     so that tlfea_mesh_set_material and tlfea_mesh_set_precision cause no
+ *     allocation there.
  *   tlfea_assemble_nodes: per node, the sums of Eqs. fint_local / fint_global
  *     and Eq. tangent_block over the incident elements, written to d_f and / or
  *     d_vals (either may be NULL; d_vals needs want_tangent = 1); accumulate

@@ -40,6 +40,7 @@
 #include <utility>
 
 #include "kernel_common.h"
+#include "work_buffer.h"
 
 // work area of the allocation-free force call, one copy per device
 static __device__ __align__(256) unsigned char scratch[TLFEA_NOALLOC_SCRATCH_BYTES];
@@ -2468,9 +2469,17 @@ bool use_rows_batch(const Mesh& m, int64_t n_elem) {
   return m.elem_type == TLFEA_ANCF3243 || m.gl[0] != 3 || n_elem >= kRows64MinShell;
 }
 
+static size_t rows_bytes(const Mesh& m) {
+  const size_t r = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
+  return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * r;
+}
+
+static size_t record_bytes(const Mesh& m) { return (size_t)m.n_elem * m.n_qp * stage_record_bytes(m.precision); }
+
 bool use_rows(const Mesh& m, bool want_k) {
-  return want_k && use_rows_batch(m, m.n_elem) &&
-         (m.precision == TLFEA_MIXED || m.elem_type != TLFEA_T10 || !sym_records(m));
+  if (!want_k || !use_rows_batch(m, m.n_elem)) return false;
+  if (m.precision == TLFEA_MIXED) return true;
+  return (m.elem_type != TLFEA_T10 || !sym_records(m)) && buffer_takes_rows(rows_bytes(m), record_bytes(m), m.stage_cap);
 }
 
 // The float64 point records of a tangent pass take the symmetric layout for
@@ -2488,10 +2497,10 @@ bool use_force_blocks(const Mesh& m, bool want_k) {
 }
 
 size_t stage_bytes(const Mesh& m, bool want_k) {
+  if (use_rows(m, want_k)) return rows_bytes(m);
   const size_t r = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
-  if (use_rows(m, want_k)) return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * r;
   if (use_force_blocks(m, want_k)) return (size_t)m.n_elem * m.n_pn * 3 * m.mc * r;
-  return (size_t)m.n_elem * m.n_qp * (want_k ? kRecK : kRecF) * r;
+  return want_k ? record_bytes(m) : (size_t)m.n_elem * m.n_qp * kRecF * r;
 }
 
 int lpt_tile_elems() { return kLptTile; }
