@@ -252,7 +252,7 @@ int tlfea_assemble_upper(tlfea_mesh_t mesh, const double* d_q, const double* d_q
  *     per-point form; a buffer that already holds the latter (the mesh's tangent
  *     ran undamped, or in mixed precision) is kept and the per-point form taken,
  *     so that tlfea_mesh_set_material and tlfea_mesh_set_precision cause no
- *     allocation there.
+ *     allocation there; likewise where the device has no memory for the rows.
  *   tlfea_assemble_nodes: per node, the sums of Eqs. fint_local / fint_global
  *     and Eq. tangent_block over the incident elements, written to d_f and / or
  *     d_vals (either may be NULL; d_vals needs want_tangent = 1); accumulate

@@ -2496,6 +2496,10 @@ bool use_force_blocks(const Mesh& m, bool want_k) {
   return on && !want_k && m.d_incpos;
 }
 
+size_t stage_bytes_min(const Mesh& m, bool want_k) {
+  return want_k && m.precision == TLFEA_FP64 ? record_bytes(m) : stage_bytes(m, want_k);
+}
+
 size_t stage_bytes(const Mesh& m, bool want_k) {
   if (use_rows(m, want_k)) return rows_bytes(m);
   const size_t r = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "tlfea_internal.h"
+#include "work_buffer.h"
 
 using tlfea::BatchArgs;
 using tlfea::BatchBody;
@@ -305,12 +306,18 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
     b->generation.push_back(m.generation);
   }
   if (b->n_blocks > INT32_MAX || b->n_rblocks > INT32_MAX) { delete b; return TLFEA_ERR_TOO_LARGE; }
-  const size_t stage = b->rows ? (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->precision)
-                               : (size_t)b->n_points * tlfea::stage_record_bytes(b->precision);
+  const size_t records = (size_t)b->n_points * tlfea::stage_record_bytes(b->precision);
+  const size_t rows = (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->precision);
+  const size_t stage = b->rows ? rows : records;
   if (hipSetDevice(b->device) != hipSuccess) { delete b; return TLFEA_ERR_HIP; }
   if (hipMalloc(&b->d_bodies, sizeof(BatchBody) * bodies.size()) != hipSuccess ||
-      hipMalloc(&b->d_stage, stage > 0 ? stage : 1) != hipSuccess ||
-      hipMalloc(&b->d_flags, sizeof(uint32_t)) != hipSuccess) {
+      hipMalloc(&b->d_flags, sizeof(uint32_t)) != hipSuccess ||
+      tlfea::take_buffer(stage, b->precision == TLFEA_FP64 ? records : stage, [&](size_t bytes) {
+        const bool ok = hipMalloc(&b->d_stage, bytes > 0 ? bytes : 1) == hipSuccess;
+        if (ok && bytes < rows) b->rows = 0;
+        if (!ok) (void)hipGetLastError();
+        return ok ? TLFEA_OK : TLFEA_ERR_NOMEM;
+      }) != TLFEA_OK) {
     (void)hipGetLastError();
     batch_free(b);
     return TLFEA_ERR_NOMEM;

@@ -11,6 +11,7 @@
 
 #include "rules.h"
 #include "tlfea_internal.h"
+#include "work_buffer.h"
 
 namespace tlfea {
 namespace {
@@ -496,7 +497,9 @@ static int run_points(tlfea_mesh_t mesh, const double* q, const double* qdot, do
   Mesh& m = mesh->m;
   auto s = (hipStream_t)stream;
   m.last_stream = s;
-  if ((rc = tlfea::ensure_stage(m, tlfea::stage_bytes(m, want_k)))) return rc;
+  rc = tlfea::take_buffer(tlfea::stage_bytes(m, want_k), tlfea::stage_bytes_min(m, want_k),
+                          [&](size_t bytes) { return tlfea::ensure_stage(m, bytes); });
+  if (rc) return rc;
   tlfea::AsmArgs a = tlfea::make_args(m, q, qdot, nullptr, nullptr, alpha, beta);
   rc = tlfea::launch_points(m, a, want_k, s);
   m.staged = rc ? 0 : (want_k ? (tlfea::use_rows(m, true) ? 3 : 2) : (tlfea::use_force_blocks(m, false) ? 4 : 1));

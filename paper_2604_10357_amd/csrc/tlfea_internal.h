@@ -318,6 +318,7 @@ bool point_records_sym(const Mesh& m, bool want_k);
 // pass 1 leaves one float-or-double force block of 3 mc values per incidence.
 bool use_force_blocks(const Mesh& m, bool want_k);
 size_t stage_bytes(const Mesh& m, bool want_k);
+size_t stage_bytes_min(const Mesh& m, bool want_k);  // the same where memory is short (the point records' in float64)
 size_t stage_record_bytes(int precision);
 int lpt_tile_elems();      // elements per item of the persistent batch schedule (the default)
 size_t row_block_bytes_for(int elem_type, int precision);  // element-row path: bytes per (element, node) row block

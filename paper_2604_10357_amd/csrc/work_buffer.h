@@ -4,6 +4,8 @@
 
 #include <cstddef>
 
+#include "../../include/tlfea.h"
+
 namespace tlfea {
 
 // Element rows are the faster form of a large mesh, but they may be larger than
@@ -14,6 +16,15 @@ namespace tlfea {
 // handle still names the same memory.
 inline bool buffer_takes_rows(size_t rows, size_t records, size_t cap) {
   return cap >= rows || cap < records;
+}
+
+// Takes `need` bytes, or where the device does not have them the `smaller` form's:
+// a mesh that fits with its point records runs with them.  take(bytes) returns a
+// status.
+template <class Take>
+int take_buffer(size_t need, size_t smaller, Take&& take) {
+  const int rc = take(need);
+  return rc == TLFEA_ERR_NOMEM && smaller < need ? take(smaller) : rc;
 }
 
 }  // namespace tlfea
