@@ -2524,6 +2524,10 @@ int row_elems_for(int elem_type, int gl0, int precision, int64_t n_elem) {
   return gl0 == 3 ? mc_elems<RuleAncf<3, 3, 2>>(precision) : mc_elems<RuleAncf<4, 4, 3>>(precision);
 }
 
+int schedule_tile(int elem_type, int gl0) {
+  return elem_type == TLFEA_T10 ? kLptTile : row_elems_for(elem_type, gl0, TLFEA_MIXED, 0);
+}
+
 size_t stage_record_bytes(int precision) {
   return (size_t)kRecK * (precision == TLFEA_MIXED ? sizeof(float) : sizeof(double));
 }

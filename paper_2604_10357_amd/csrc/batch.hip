@@ -481,7 +481,9 @@ TLFEA_API int tlfea_batch_get_schedule(tlfea_batch_t b, int32_t* persistent, int
   if (!b) return TLFEA_ERR_INVALID;
   const tlfea::BatchSchedule& sc = b->sched;
   if (persistent) *persistent = sc.persistent;
-  if (tile_elems) *tile_elems = sc.persistent ? sc.tile_elems : b->row_tile;
+  // per item: the tile that a change to the persistent schedule may start from (the
+  // launches' own tile is smaller and follows the batch's size)
+  if (tile_elems) *tile_elems = sc.persistent ? sc.tile_elems : tlfea::schedule_tile(b->elem_type, b->gl0);
   if (grid_tiles) *grid_tiles = sc.persistent ? sc.grid_tiles : (int32_t)b->n_rblocks;
   if (grid_ranges) *grid_ranges = sc.persistent ? sc.grid_ranges : b->n_ranges;
   return TLFEA_OK;
