@@ -36,6 +36,10 @@ constexpr int kNormBlocks = 256;
 // 29.4 against 19.9; 18,000 elements, 26 iterations: 38.1 against 29.5).
 constexpr int kMinReplays = 8;
 
+// Iterations whose divisors are tabulated at a time: the table stays 64 KiB however
+// rarely the caller checks.
+constexpr int kCorrTable = 4096;
+
 struct AdamwArgs {
   double lr, beta1, beta2, eps, wd, h;
 };
@@ -168,18 +172,14 @@ TLFEA_API int tlfea_adamw_solve(tlfea_mesh_t mesh, const tlfea_adamw_params* p, 
   double* g = d_work + 2 * n;
   double* f = d_work + 3 * n;
   // device scalars: iteration counter, norm partials and norms, then the
-  // bias-correction divisors of the iterations between two checks
-  const int32_t longest = std::min(check_every, max_iters);
-  const size_t scalars = 2 * tlfea::kNormBlocks + 6, need = scalars + 2 * (size_t)longest;
-  if (m.solver_cap < need) {
-    double* d = nullptr;
-    if (hipMalloc(&d, sizeof(double) * need) != hipSuccess) {
+  // bias-correction divisors of the next iterations
+  const size_t scalars = 2 * tlfea::kNormBlocks + 6;
+  if (!m.d_solver) {
+    if (hipMalloc(&m.d_solver, sizeof(double) * (scalars + 2 * tlfea::kCorrTable)) != hipSuccess) {
       (void)hipGetLastError();
+      m.d_solver = nullptr;
       return TLFEA_ERR_NOMEM;
     }
-    (void)hipFree(m.d_solver);  // synchronises with work that may still use it
-    m.d_solver = d;
-    m.solver_cap = need;
   }
   auto* d_l = reinterpret_cast<int64_t*>(m.d_solver);
   double* part = m.d_solver + 3;
@@ -191,11 +191,15 @@ TLFEA_API int tlfea_adamw_solve(tlfea_mesh_t mesh, const tlfea_adamw_params* p, 
   hipLaunchKernelGGL(tlfea::k_fill, dim3(1), dim3(64), 0, s, m.d_solver, (int64_t)1);
   TLFEA_HIP_CHECK(hipGetLastError());
   auto iterations = [&](int32_t count) -> int {
-    hipLaunchKernelGGL(tlfea::k_corr, dim3(1), dim3(256), 0, s, a, d_l, count, corr);
-    TLFEA_HIP_CHECK(hipGetLastError());
     int rc = TLFEA_OK;
-    for (int32_t i = 0; i < count && !rc; ++i)
-      rc = adamw_iteration(mesh, a, d_q_n, d_v_n, d_f_ext, d_v, d_q, mom, sec, g, f, corr + 2 * i, s);
+    for (int32_t done = 0; done < count && !rc;) {
+      const int32_t n_corr = std::min<int32_t>(count - done, tlfea::kCorrTable);
+      hipLaunchKernelGGL(tlfea::k_corr, dim3(1), dim3(256), 0, s, a, d_l, n_corr, corr);
+      TLFEA_HIP_CHECK(hipGetLastError());
+      for (int32_t i = 0; i < n_corr && !rc; ++i)
+        rc = adamw_iteration(mesh, a, d_q_n, d_v_n, d_f_ext, d_v, d_q, mom, sec, g, f, corr + 2 * i, s);
+      done += n_corr;
+    }
     return rc;
   };
   auto norms_to_host = [&](double* out) -> int {
