@@ -778,6 +778,13 @@ constexpr int kRowElems = 12;           // most elements of a pass-1 workgroup: 
 // two that spill 81 to scratch (pass 1 of 480,000 elements 1.03 against 1.11 ms).
 template <typename R>
 constexpr int row_min_waves() { return sizeof(R) == 4 ? 2 : 1; }
+// Row blocks up to this size in all go through the caches, where pass 2 finds them
+// (the memory-side cache holds 256 MB); larger ones are stored past them, which
+// pass 1 gains from.  Whole call, through / past, of n damped (undamped) elements:
+// 18,000 52 / 55 (51 / 54) us, 30,000 80 / 86 (82 / 87), 33,000 85 / 90 (103 / 93),
+// 36,000 99 / 93 (107 / 100), 480,000 1,194 / 1,134 (1,224 / 1,181): the line is at
+// 32,768 elements.
+constexpr size_t kCachedRowBytes = (size_t)120 << 20;
 constexpr int kLptTile = 25;            // elements per item of the persistent batch schedule (or 16)
 // undamped materials, float32
 constexpr int kSymElems = 25;           // elements per pass-1 workgroup
@@ -790,6 +797,14 @@ constexpr int kDnL = 20;                // LDS stride of a node's gradient row (
                                         // of the ten nodes on different banks)
 constexpr int kStgL = 100;              // LDS stride of a staged row block (96 used; spreads the banks)
 
+// One piece of a row block on its way to pass 2, past the caches (NT) or through
+// them (a template argument: a branch on a value is merged into one plain store).
+template <bool NT, typename V>
+__device__ __forceinline__ void store_piece(V v, V* p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // Phase B of the element rows for a symmetric tangent (undamped materials):
 // K_e^(ki)[b, a] = K_e^(ik)[a, b], so only the slots i <= k are contracted.
 // A wave takes one element at a time, a lane per task (node a, slot i <= k):
@@ -799,7 +814,7 @@ constexpr int kStgL = 100;              // LDS stride of a staged row block (96 
 // of the parts Phat_ik dN_a,k of the node's lanes, in a fixed order.  Then the
 // wave stores the ten blocks with 16-byte stores of consecutive lanes.  Two
 // thirds of the multiply-adds of the full contraction.
-template <class Rule, int EB>
+template <class Rule, bool NT>
 __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict__ incpos, float* __restrict__ rows,
                                                        int64_t e0, int ne, const float* rec, const float* dn,
                                                        float* stage_buf) {
@@ -872,8 +887,8 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
       const int pc = lane + 64 * u, bl = pc / (kRowBlk / 4), pi = pc - bl * (kRowBlk / 4);
       const int32_t pb = __shfl(my_pos, bl < NEN ? bl : 0, 64);
       if (bl < NEN)
-        __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(stg + bl * kStgL + 4 * pi),
-                                    reinterpret_cast<f32x4*>(rows + (int64_t)pb * kRowBlk + 4 * pi));
+        store_piece<NT>(*reinterpret_cast<const f32x4*>(stg + bl * kStgL + 4 * pi),
+                        reinterpret_cast<f32x4*>(rows + (int64_t)pb * kRowBlk + 4 * pi));
     }
   }
 }
@@ -881,7 +896,7 @@ __device__ __forceinline__ void elem_rows_sym_contract(const int32_t* __restrict
 // Symmetric tangent (undamped materials, float32): 25 elements in two waves,
 // the 64-value records of all their points in LDS.  480,000 elements: 0.580 ms
 // with plain stores, 0.466 with non-temporal ones.
-template <class Rule>
+template <class Rule, bool NT>
 __global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, int tile,
                                                               const int32_t* __restrict__ incpos,
                                                               float* __restrict__ rows) {
@@ -929,7 +944,7 @@ __global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, int ti
     });
   }
   __syncthreads();
-  elem_rows_sym_contract<Rule, EB>(incpos, rows, e0, ne, rec, dn, stage_buf);
+  elem_rows_sym_contract<Rule, NT>(incpos, rows, e0, ne, rec, dn, stage_buf);
 }
 
 // The row blocks of elements e0 .. e0 + ne - 1 (ne <= kRowElems), one wave.
@@ -941,15 +956,15 @@ __global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, int ti
 // both nodes, contracts the five points, and the 40 rows leave through LDS
 // with 16-byte stores of consecutive lanes (whole cache lines).  A single wave
 // needs no barrier, and waves in different phases share a SIMD.
-// The stores are non-temporal: no line is written twice or read by this pass,
-// and through the L2 (4 MB against the 13 MB that one XCD's waves have in
-// flight) they left in an order that HBM took at 3.3 TB/s.
+// Large meshes' stores are non-temporal (NT; kCachedRowBytes): no line is written
+// twice or read by this pass, and through the L2 (4 MB against the 13 MB that one
+// XCD's waves have in flight) they left in an order that HBM took at 3.3 TB/s.
 // Bound by instruction issue (5,000 a wave, 66 % of it) and by the 1.84 GB of
 // stores.  480,000 elements, float32: 0.672 ms with two-wave workgroups of 25
 // elements and whole records in LDS (53 KB, 1.5 waves per SIMD), 0.565 row by
 // row in single waves, 0.465 with non-temporal stores; without any store it
 // takes 0.375.  One node per lane, held to three waves per SIMD, is as fast.
-template <class Rule, typename R>
+template <class Rule, typename R, bool NT>
 __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
                                                R* __restrict__ rows, int64_t e0, int ne) {
   static_assert(Rule::MC == 1 && Rule::NEN == 10 && 3 * kSlot <= kRowChunk, "element rows are built for T10");
@@ -1067,24 +1082,23 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
           V v;
 #pragma unroll
           for (int t = 0; t < PER; ++t) v[t] = src[t / 2][t % 2];
-          __builtin_nontemporal_store(
-              v, reinterpret_cast<V*>(rows + (int64_t)pos[g0 * NEN + bl] * kRowBlk + kRowChunk * i + PER * pi));
+          store_piece<NT>(v, reinterpret_cast<V*>(rows + (int64_t)pos[g0 * NEN + bl] * kRowBlk + kRowChunk * i + PER * pi));
         }
       }
     }
   });
 }
 
-template <class Rule, typename R>
+template <class Rule, typename R, bool NT>
 __global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows(AsmArgs a, int tile,
                                                                            const int32_t* __restrict__ incpos,
                                                                            R* __restrict__ rows) {
   const int64_t e0 = (int64_t)blockIdx.x * tile;
-  elem_rows_tile<Rule, R>(a, incpos, rows, e0, (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile));
+  elem_rows_tile<Rule, R, NT>(a, incpos, rows, e0, (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile));
 }
 
 // many bodies: every body starts on a workgroup of its own, found by bisection
-template <class Rule, typename R>
+template <class Rule, typename R, bool NT>
 __global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows_batch(BatchArgs b) {
   const int64_t blk = blockIdx.x;
   int lo = 0, hi = b.n_bodies - 1;
@@ -1095,7 +1109,7 @@ __global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows_batch(Ba
   const BatchBody& B = b.bodies[lo];
   const AsmArgs a = body_args(b, B, lo);
   const int64_t e0 = (blk - B.rblock_off) * b.row_tile;
-  elem_rows_tile<Rule, R>(a, B.incpos, (R*)b.stage + B.blk_inc_off * kRowBlk, e0,
+  elem_rows_tile<Rule, R, NT>(a, B.incpos, (R*)b.stage + B.blk_inc_off * kRowBlk, e0,
                           (int)(a.n_elem - e0 < b.row_tile ? a.n_elem - e0 : b.row_tile));
 }
 
@@ -1103,7 +1117,7 @@ __global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows_batch(Ba
 // GPU holds at once, whose workgroups take (body, tile) items from a counter
 // in a list ordered longest first (full tiles of the largest bodies first,
 // partial tiles last), EB elements per tile, which the wave takes in equal parts.
-template <class Rule, int EB>
+template <class Rule, int EB, bool NT>
 __global__ __launch_bounds__(64, 2) void k_elem_rows_batch_lpt(BatchArgs b, const int2* __restrict__ items,
                                                                     int n_items, unsigned* __restrict__ counter) {
   __shared__ int item;
@@ -1121,7 +1135,7 @@ __global__ __launch_bounds__(64, 2) void k_elem_rows_batch_lpt(BatchArgs b, cons
 #pragma unroll 1
     for (int64_t e0 = (int64_t)t.y * EB; e0 < end; e0 += step) {
       wave_sync();  // the previous part's LDS is consumed
-      elem_rows_tile<Rule, float>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, e0,
+      elem_rows_tile<Rule, float, NT>(a, B.incpos, (float*)b.stage + B.blk_inc_off * kRowBlk, e0,
                                   (int)(end - e0 < step ? end - e0 : step));
     }
   }
@@ -2474,6 +2488,8 @@ static size_t rows_bytes(const Mesh& m) {
   return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * r;
 }
 
+bool rows_past_caches(size_t bytes) { return bytes > kCachedRowBytes; }
+
 static size_t record_bytes(const Mesh& m) { return (size_t)m.n_elem * m.n_qp * stage_record_bytes(m.precision); }
 
 bool use_rows(const Mesh& m, bool want_k) {
@@ -2534,14 +2550,16 @@ size_t stage_record_bytes(int precision) {
 
 // Workgroups of the persistent batch kernels one CU holds at once (tile kernel
 // for EB elements per tile; range kernel for the given shape and LDS bytes).
-int batch_lpt_occupancy(int tile_elems, int waves, size_t lds_all, int* tiles_per_cu, int* ranges_per_cu) {
+using LptKernel = void (*)(BatchArgs, const int2*, int, unsigned*);
+static LptKernel lpt_kernel(int tile_elems, bool nt) {
+  if (tile_elems == 16) return nt ? k_elem_rows_batch_lpt<RuleT10, 16, true> : k_elem_rows_batch_lpt<RuleT10, 16, false>;
+  return nt ? k_elem_rows_batch_lpt<RuleT10, kLptTile, true> : k_elem_rows_batch_lpt<RuleT10, kLptTile, false>;
+}
+
+int batch_lpt_occupancy(int tile_elems, bool rows_nt, int waves, size_t lds_all, int* tiles_per_cu, int* ranges_per_cu) {
   int nt = 0, nr = 0;
-  if (tile_elems == 16)
-    TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, 16>), 64, 0));
-  else
-    TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nt, reinterpret_cast<const void*>(k_elem_rows_batch_lpt<RuleT10, kLptTile>), 64, 0));
+  TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &nt, reinterpret_cast<const void*>(lpt_kernel(tile_elems, rows_nt)), 64, 0));
   if (int rc = allow_lds(k_gather_rows_batch_lpt, lds_all)) return rc;
   TLFEA_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(
       &nr, reinterpret_cast<const void*>(k_gather_rows_batch_lpt), 64 * waves, lds_all));
@@ -2574,14 +2592,16 @@ int launch_points(const Mesh& m, const AsmArgs& a, bool want_k, hipStream_t s) {
     const int64_t blocks = (m.n_elem + tile - 1) / tile;
     if (blocks > INT32_MAX) return TLFEA_ERR_TOO_LARGE;
     if (blocks > 0) {
+      const dim3 grid((unsigned)blocks);
+      const bool nt = rows_past_caches(rows_bytes(m));
       if (sym)
-        hipLaunchKernelGGL(k_elem_rows_sym<RuleT10>, dim3((unsigned)blocks), dim3(kSymThreads), 0, s, a, tile, m.d_incpos,
-                           (float*)m.d_stage);
+        hipLaunchKernelGGL((nt ? k_elem_rows_sym<RuleT10, true> : k_elem_rows_sym<RuleT10, false>), grid,
+                           dim3(kSymThreads), 0, s, a, tile, m.d_incpos, (float*)m.d_stage);
       else if (m.precision == TLFEA_MIXED)
-        hipLaunchKernelGGL((k_elem_rows<RuleT10, float>), dim3((unsigned)blocks), dim3(64), 0, s, a, tile, m.d_incpos,
-                           (float*)m.d_stage);
-      else
-        hipLaunchKernelGGL((k_elem_rows<RuleT10, double>), dim3((unsigned)blocks), dim3(64), 0, s, a, tile, m.d_incpos,
+        hipLaunchKernelGGL((nt ? k_elem_rows<RuleT10, float, true> : k_elem_rows<RuleT10, float, false>), grid, dim3(64), 0,
+                           s, a, tile, m.d_incpos, (float*)m.d_stage);
+      else  // float64 rows start far above the cached size
+        hipLaunchKernelGGL((k_elem_rows<RuleT10, double, true>), grid, dim3(64), 0, s, a, tile, m.d_incpos,
                            (double*)m.d_stage);
     }
     TLFEA_HIP_CHECK(hipGetLastError());
@@ -2684,8 +2704,14 @@ int launch_params(const Mesh& m, const double* d_params, hipStream_t s) {
 
 template <typename R>
 int launch_rows_batch(const GatherTuning& tu, const BatchArgs& b, int n_ranges, size_t lds, hipStream_t s) {
-  if (b.n_rblocks > 0)
-    hipLaunchKernelGGL((k_elem_rows_batch<RuleT10, R>), dim3((unsigned)b.n_rblocks), dim3(64), 0, s, b);
+  // float64 rows start far above the cached size
+  if (b.n_rblocks > 0) {
+    const dim3 grid((unsigned)b.n_rblocks);
+    if (sizeof(R) == 8 || b.nt)
+      hipLaunchKernelGGL((k_elem_rows_batch<RuleT10, R, true>), grid, dim3(64), 0, s, b);
+    else
+      hipLaunchKernelGGL((k_elem_rows_batch<RuleT10, float, false>), grid, dim3(64), 0, s, b);
+  }
   TLFEA_HIP_CHECK(hipGetLastError());
   const size_t lds_all = lds + b.inc_cap;
   if (int rc = allow_lds(k_gather_rows_batch<R>, lds_all)) return rc;
@@ -2728,14 +2754,9 @@ int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tu, 
   if (n_ranges == 0) return TLFEA_OK;
   if (b.rows && sc.persistent) {
     hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, s, sc.counters);
-    if (sc.n_tiles > 0) {
-      if (sc.tile_elems == 16)
-        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, 16>), dim3(sc.grid_tiles), dim3(64), 0, s, b,
-                           sc.tiles, sc.n_tiles, sc.counters);
-      else
-        hipLaunchKernelGGL((k_elem_rows_batch_lpt<RuleT10, kLptTile>), dim3(sc.grid_tiles), dim3(64), 0, s,
-                           b, sc.tiles, sc.n_tiles, sc.counters);
-    }
+    if (sc.n_tiles > 0)
+      hipLaunchKernelGGL(lpt_kernel(sc.tile_elems, b.nt != 0), dim3(sc.grid_tiles), dim3(64), 0, s, b, sc.tiles,
+                         sc.n_tiles, sc.counters);
     TLFEA_HIP_CHECK(hipGetLastError());
     const size_t lds_all = lds + b.inc_cap;
     if (int rc = allow_lds(k_gather_rows_batch_lpt, lds_all)) return rc;

@@ -36,6 +36,7 @@ struct tlfea_batch_s {
   int rows = 0;                      // element-row path (mixed; persistent schedule for T10)
   int64_t n_inc = 0, n_rblocks = 0;  // its row blocks and pass-1 workgroups
   int row_tile = 1;                  // elements of a pass-1 workgroup
+  int rows_nt = 0;                   // T10: the row blocks are stored past the caches
   size_t lds = 0;
   int inc_cap = 0;
   void* d_stage = nullptr;
@@ -138,7 +139,7 @@ static int batch_plan_lpt(tlfea_batch_s* b, int tile_elems) {
   }
   int cus = 0, per_tile = 1, per_range = 1;
   TLFEA_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
-  if ((rc = tlfea::batch_lpt_occupancy(tile_elems, b->tune.waves, b->lds + b->inc_cap, &per_tile, &per_range)))
+  if ((rc = tlfea::batch_lpt_occupancy(tile_elems, b->rows_nt != 0, b->tune.waves, b->lds + b->inc_cap, &per_tile, &per_range)))
     return rc;
   tlfea::BatchSchedule& sc = b->sched;
   sc.persistent = 1;
@@ -309,6 +310,7 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
   const size_t records = (size_t)b->n_points * tlfea::stage_record_bytes(b->precision);
   const size_t rows = (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->precision);
   const size_t stage = b->rows ? rows : records;
+  b->rows_nt = tlfea::rows_past_caches(rows) ? 1 : 0;
   if (hipSetDevice(b->device) != hipSuccess) { delete b; return TLFEA_ERR_HIP; }
   if (hipMalloc(&b->d_bodies, sizeof(BatchBody) * bodies.size()) != hipSuccess ||
       hipMalloc(&b->d_flags, sizeof(uint32_t)) != hipSuccess ||
@@ -381,6 +383,7 @@ static BatchArgs batch_args(tlfea_batch_t b, const double* d_q, const double* d_
   a.n_blocks = b->n_blocks;
   a.n_rblocks = b->n_rblocks;
   a.row_tile = b->row_tile;
+  a.nt = b->rows_nt;
   a.rows = b->rows;
   a.inc_cap = b->inc_cap;
   a.stage = b->d_stage;

@@ -274,6 +274,7 @@ struct BatchArgs {
   int64_t n_points, n_blocks;
   int64_t n_rblocks;  // pass-1 workgroups of the element-row path
   int row_tile;       // T10: elements of each (ANCF tiles have a fixed size)
+  int nt;             // T10: the row blocks are stored past the caches
   int rows;           // 1: element-row path (T10, mixed), 0: per-point records
   void* stage;
   const double* q;
@@ -299,7 +300,7 @@ struct BatchSchedule {
   unsigned* counters = nullptr;
   int grid_tiles = 0, grid_ranges = 0;
 };
-int batch_lpt_occupancy(int tile_elems, int waves, size_t lds_all, int* tiles_per_cu, int* ranges_per_cu);
+int batch_lpt_occupancy(int tile_elems, bool rows_nt, int waves, size_t lds_all, int* tiles_per_cu, int* ranges_per_cu);
 
 MatParams make_params(int material, const double* params, double eta, double lam_v);
 
@@ -322,6 +323,7 @@ size_t stage_record_bytes(int precision);
 int lpt_tile_elems();      // elements per item of the persistent batch schedule (the default)
 size_t row_block_bytes_for(int elem_type, int precision);  // element-row path: bytes per (element, node) row block
 int row_elems_for(int elem_type, int gl0, int precision, int64_t n_elem);  // elements per pass-1 workgroup (n_elem: of the launch)
+bool rows_past_caches(size_t bytes);  // T10 row blocks of this size in all are stored past the caches
 int schedule_tile(int elem_type, int gl0);  // tile_elems reported for a batch that runs per item
 int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tune, const BatchArgs& b,
                  int n_ranges, size_t lds, hipStream_t s, const BatchSchedule& sc);
