@@ -2470,17 +2470,24 @@ constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
 // float64 element rows of the 3x3x2 shell: a workgroup's 21 slot tiles are a chain
 // that a small mesh waits for (65 elements 44 us with rows, 33 with records; 1,024
 // elements 53 / 43); with every CU busy the rows win (4,096 elements 86 / 92,
-// 10,000 damped 190 / 220, 65,536 1,003 / 1,166).  The beam and the 4x4x3 shell,
-// whose records are the larger (8.8 and 35 KB an element against 5.2 and 19.6),
-// take rows at every size (beam: 100 elements 22 / 25, 500,000 2,140 / 2,825;
-// 4x4x3: 64 elements 39 / 71, 10,000 257 / 434).
+// 10,000 damped 190 / 220, 65,536 1,003 / 1,166).  The 4x4x3 shell, whose records
+// are the larger (35 KB an element against 19.6), takes rows at every size (1
+// element 18 / 40 us, 64 39 / 71, 10,000 257 / 434).
 constexpr int64_t kRows64MinShell = 3000;
+
+// float64 element rows of the beam: one wave's chain takes 14 us, which the records
+// of a few elements undercut, the symmetric ones of an undamped mesh those of a few
+// more (rows / records: damped 3 elements 18.3 / 16.8 us, 4 19.0 / 20.4, 8 21.0 /
+// 25.2; undamped 1 16.3 / 12.8, 6 19.1 / 18.4, 8 20.0 / 22.1, 100 22 / 25, 500,000
+// 2,140 / 2,825).  Batches have full records, so the first line holds for them.
+constexpr int64_t kRows64MinBeam = 4, kRows64MinBeamSym = 8;
 
 bool use_rows_batch(const Mesh& m, int64_t n_elem) {
   if (!rows_on() || !m.d_incpos || (m.elem_type == TLFEA_T10 && !m.d_rank_inc)) return false;
   if (m.precision == TLFEA_MIXED) return true;
   if (m.elem_type == TLFEA_T10) return n_elem >= kRows64MinElems && rows_addressable(m, sizeof(double));
-  return m.elem_type == TLFEA_ANCF3243 || m.gl[0] != 3 || n_elem >= kRows64MinShell;
+  if (m.elem_type == TLFEA_ANCF3243) return n_elem >= kRows64MinBeam;
+  return m.gl[0] != 3 || n_elem >= kRows64MinShell;
 }
 
 static size_t rows_bytes(const Mesh& m) {
@@ -2495,7 +2502,9 @@ static size_t record_bytes(const Mesh& m) { return (size_t)m.n_elem * m.n_qp * s
 bool use_rows(const Mesh& m, bool want_k) {
   if (!want_k || !use_rows_batch(m, m.n_elem)) return false;
   if (m.precision == TLFEA_MIXED) return true;
-  return (m.elem_type != TLFEA_T10 || !sym_records(m)) && buffer_takes_rows(rows_bytes(m), record_bytes(m), m.stage_cap);
+  if (sym_records(m) && (m.elem_type == TLFEA_T10 || (m.elem_type == TLFEA_ANCF3243 && m.n_elem < kRows64MinBeamSym)))
+    return false;
+  return buffer_takes_rows(rows_bytes(m), record_bytes(m), m.stage_cap);
 }
 
 // The float64 point records of a tangent pass take the symmetric layout for
@@ -2517,7 +2526,8 @@ size_t stage_bytes_min(const Mesh& m, bool want_k) {
 }
 
 size_t stage_bytes(const Mesh& m, bool want_k) {
-  if (use_rows(m, want_k)) return rows_bytes(m);
+  // between the beam's lines the form follows the material: the buffer fits both
+  if (use_rows(m, want_k)) return m.n_elem < kRows64MinBeamSym ? std::max(rows_bytes(m), record_bytes(m)) : rows_bytes(m);
   const size_t r = m.precision == TLFEA_MIXED ? sizeof(float) : sizeof(double);
   if (use_force_blocks(m, want_k)) return (size_t)m.n_elem * m.n_pn * 3 * m.mc * r;
   return want_k ? record_bytes(m) : (size_t)m.n_elem * m.n_qp * kRecF * r;
