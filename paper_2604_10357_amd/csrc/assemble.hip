@@ -785,6 +785,10 @@ constexpr int row_min_waves() { return sizeof(R) == 4 ? 2 : 1; }
 // 36,000 99 / 93 (107 / 100), 480,000 1,194 / 1,134 (1,224 / 1,181): the line is at
 // 32,768 elements.
 constexpr size_t kCachedRowBytes = (size_t)120 << 20;
+// Damped float32 tiles up to this many take a workgroup for each row component: two
+// waves a SIMD.  Whole call, in one / in three workgroups a tile: 6 elements 15.4 /
+// 11.4 us, 270 17.5 / 13.2, 600 17.2 / 15.4, 1,020 18.1 / 20.1 (a tile each).
+constexpr int64_t kSplitRowTiles = 682;
 constexpr int kLptTile = 25;            // elements per item of the persistent batch schedule (or 16)
 // undamped materials, float32
 constexpr int kSymElems = 25;           // elements per pass-1 workgroup
@@ -964,9 +968,10 @@ __global__ __launch_bounds__(kSymThreads) void k_elem_rows_sym(AsmArgs a, int ti
 // elements and whole records in LDS (53 KB, 1.5 waves per SIMD), 0.565 row by
 // row in single waves, 0.465 with non-temporal stores; without any store it
 // takes 0.375.  One node per lane, held to three waves per SIMD, is as fast.
-template <class Rule, typename R, bool NT>
+// ONE: only row component `row` is formed (k_elem_rows).
+template <class Rule, typename R, bool NT, bool ONE = false>
 __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* __restrict__ incpos,
-                                               R* __restrict__ rows, int64_t e0, int ne) {
+                                               R* __restrict__ rows, int64_t e0, int ne, int row = 0) {
   static_assert(Rule::MC == 1 && Rule::NEN == 10 && 3 * kSlot <= kRowChunk, "element rows are built for T10");
   constexpr int NQ = Rule::NQ, NEN = Rule::NEN, EB = kRowElems;
   constexpr int Z = sizeof(R) == 4 ? 2 : 1, HN = NEN / Z;  // nodes per lane, lanes per (element, component)
@@ -1008,6 +1013,7 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
   const int eg = lane / (3 * HN), an = (lane - 3 * HN * eg) / 3, k = lane % 3;  // lanes 60 .. 63: eg = GRP, idle
   sfor<0, 3>([&](auto ic) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value;
+    if (ONE && i != row) return;  // uniform
     wave_sync();  // the previous row's slots are consumed
     if (act) {
       R* r = rec + pl * RS;
@@ -1089,12 +1095,15 @@ __device__ __forceinline__ void elem_rows_tile(const AsmArgs& a, const int32_t* 
   });
 }
 
-template <class Rule, typename R, bool NT>
+// ONE: a workgroup for each row component of a tile (grid y), which form the points'
+// factors three times over: for a mesh that leaves most of the GPU idle the chain of
+// one wave is what it waits for.
+template <class Rule, typename R, bool NT, bool ONE = false>
 __global__ __launch_bounds__(64, (row_min_waves<R>())) void k_elem_rows(AsmArgs a, int tile,
                                                                            const int32_t* __restrict__ incpos,
                                                                            R* __restrict__ rows) {
   const int64_t e0 = (int64_t)blockIdx.x * tile;
-  elem_rows_tile<Rule, R, NT>(a, incpos, rows, e0, (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile));
+  elem_rows_tile<Rule, R, NT, ONE>(a, incpos, rows, e0, (int)(a.n_elem - e0 < tile ? a.n_elem - e0 : tile), blockIdx.y);
 }
 
 // many bodies: every body starts on a workgroup of its own, found by bisection
@@ -2607,6 +2616,9 @@ int launch_points(const Mesh& m, const AsmArgs& a, bool want_k, hipStream_t s) {
       if (sym)
         hipLaunchKernelGGL((nt ? k_elem_rows_sym<RuleT10, true> : k_elem_rows_sym<RuleT10, false>), grid,
                            dim3(kSymThreads), 0, s, a, tile, m.d_incpos, (float*)m.d_stage);
+      else if (m.precision == TLFEA_MIXED && blocks <= kSplitRowTiles)
+        hipLaunchKernelGGL((k_elem_rows<RuleT10, float, false, true>), dim3(grid.x, 3), dim3(64), 0, s, a, tile,
+                           m.d_incpos, (float*)m.d_stage);
       else if (m.precision == TLFEA_MIXED)
         hipLaunchKernelGGL((nt ? k_elem_rows<RuleT10, float, true> : k_elem_rows<RuleT10, float, false>), grid, dim3(64), 0,
                            s, a, tile, m.d_incpos, (float*)m.d_stage);

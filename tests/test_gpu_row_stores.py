@@ -1,6 +1,7 @@
-"""T10 element rows in mixed precision on both sides of the size from which their
-stores pass the caches (32,768 elements): a mesh, a batch per item and a batch
-with the persistent schedule."""
+"""T10 element rows in mixed precision on both sides of the sizes where their launch
+changes: from 32,768 elements on the stores pass the caches (a mesh, a batch per
+item and a batch with the persistent schedule), up to 682 damped tiles each row
+component has a workgroup of its own."""
 import dataclasses
 
 import pytest
@@ -35,4 +36,22 @@ def test_rows_through_and_past_the_caches(damped, n):
         assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
         assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
     b.close()
+    m.close()
+
+
+@pytest.mark.parametrize("n", [1, 681, 682, 683])
+def test_row_components_split_over_workgroups(n):
+    print(f"[gpu] split rows {n}", flush=True)
+    mat = W.Material(W.MOONEY_RIVLIN, (2e5, 5e4, 1e8), 1e3, 7e2)
+    wl = W.t10_beam(29, 2, 2, 331, "split", lx=0.3625, ly=0.025, lz=0.025, material=mat)
+    wl = dataclasses.replace(wl, mesh=dataclasses.replace(wl.mesh, conn=wl.mesh.conn[:n].copy()))
+    f_ref, v_ref = oracle.assemble(oracle.Mesh.of(wl.mesh), oracle.material_of(mat), wl.q, wl.qdot, 1e-3, 1.0)
+    m = make_mesh(wl, "mixed")
+    f, v = m.assemble(cuda(wl.q), cuda(wl.qdot), 1e-3, 1.0)
+    f_only = torch.empty_like(f)
+    m.assemble_nodes(f_only)
+    torch.cuda.synchronize()
+    assert rel_err(f.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
+    assert rel_err(f_only.cpu().numpy(), f_ref)[0] <= TOL["mixed"]
+    assert rel_err(v.cpu().numpy(), v_ref)[0] <= TOL["mixed"]
     m.close()
