@@ -388,7 +388,8 @@ int tlfea_get_runtime_flags(tlfea_mesh_t mesh, uint32_t* flags);
  * segment held in LDS) and how many waves work on a range.  Every shape gives
  * the same result up to rounding order.  The default is {4, 768, 2048} for
  * T10 meshes created in mixed precision, {8, 768, 4096} for ANCF meshes in
- * mixed precision or of 3,000 elements or more, and {4, 768, 4096} otherwise
+ * mixed precision or of 3,000 elements or more (3x3x2 shells in float64: 4,096),
+ * and {4, 768, 4096} otherwise
  * (environment TLFEA_GATHER_WAVES / TLFEA_RANGE_TASKS / TLFEA_RANGE_VALUES
  * override it when the pattern is built).
  * ------------------------------------------------------------------------- */

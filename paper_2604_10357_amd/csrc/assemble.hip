@@ -2477,13 +2477,18 @@ static bool rows_on() {
 constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
 
 // float64 element rows of the 3x3x2 shell: a workgroup's 21 slot tiles are a chain
-// that a small mesh waits for (65 elements 44 us with rows, 33 with records; 1,024
-// elements 53 / 43); with every CU busy the rows win (4,096 elements 86 / 92,
-// 10,000 damped 190 / 220, 65,536 1,003 / 1,166).  The 4x4x3 shell, whose records
-// are the larger (35 KB an element against 19.6), takes rows at every size (1
-// element 18 / 40 us, 64 39 / 71, 10,000 257 / 434).
-constexpr int64_t kRows64MinShell = 3000;
+// that a small mesh waits for.  f and K, rows / records with their four waves:
+// undamped 1,024 elements 54 / 42 us, 3,025 79 / 75, 4,096 84 / 87, 6,400 96 / 121,
+// 10,000 172 / 176, 40,000 643 / 763; damped 2,704 89 / 76, 3,025 92 / 91, 4,096 96 /
+// 111, 10,000 185 / 223.  K alone gains less (the rows hold the force anyway): damped
+// 4,096 95 / 96, undamped 83 / 79, 10,000 170 / 160, 25,600 429 / 444; the line is
+// f and K's.  Batches have full records and few elements a workgroup: 3,200 bodies of
+// one element 107 / 181, 40 of 100 104 / 113.
+constexpr int64_t kRows64MinShellBatch = 3000;
 
+// The 4x4x3 shell, whose records are the larger (35 KB an element against 19.6),
+// takes rows at every size (1 element 18 / 40 us, 64 39 / 71, 10,000 257 / 434).
+//
 // float64 element rows of the beam: one wave's chain takes 14 us, which the records
 // of a few elements undercut, the symmetric ones of an undamped mesh those of a few
 // more (rows / records: damped 3 elements 18.3 / 16.8 us, 4 19.0 / 20.4, 8 21.0 /
@@ -2496,7 +2501,7 @@ bool use_rows_batch(const Mesh& m, int64_t n_elem) {
   if (m.precision == TLFEA_MIXED) return true;
   if (m.elem_type == TLFEA_T10) return n_elem >= kRows64MinElems && rows_addressable(m, sizeof(double));
   if (m.elem_type == TLFEA_ANCF3243) return n_elem >= kRows64MinBeam;
-  return m.gl[0] != 3 || n_elem >= kRows64MinShell;
+  return m.gl[0] != 3 || n_elem >= kRows64MinShellBatch;
 }
 
 static size_t rows_bytes(const Mesh& m) {
@@ -2511,6 +2516,7 @@ static size_t record_bytes(const Mesh& m) { return (size_t)m.n_elem * m.n_qp * s
 bool use_rows(const Mesh& m, bool want_k) {
   if (!want_k || !use_rows_batch(m, m.n_elem)) return false;
   if (m.precision == TLFEA_MIXED) return true;
+  if (m.elem_type == TLFEA_ANCF3443 && m.gl[0] == 3 && m.n_elem < kRows64MinShell) return false;
   if (sym_records(m) && (m.elem_type == TLFEA_T10 || (m.elem_type == TLFEA_ANCF3243 && m.n_elem < kRows64MinBeamSym)))
     return false;
   return buffer_takes_rows(rows_bytes(m), record_bytes(m), m.stage_cap);

@@ -430,7 +430,9 @@ static int env_int(const char* name, int fallback, int lo, int hi) {
 GatherTuning gather_tuning(const Mesh& m) {
   GatherTuning t;
   if (m.elem_type == TLFEA_T10 && m.precision == TLFEA_MIXED) t.range_values = 2048;
-  if (m.elem_type != TLFEA_T10 && (m.precision == TLFEA_MIXED || m.n_elem >= 3000)) t.waves = 8;
+  const bool shell332 = m.elem_type == TLFEA_ANCF3443 && m.gl[0] == 3;
+  if (m.elem_type != TLFEA_T10 && (m.precision == TLFEA_MIXED || m.n_elem >= (shell332 ? kRows64MinShell : 3000)))
+    t.waves = 8;
   t.waves = env_int("TLFEA_GATHER_WAVES", t.waves, 1, 8);
   t.range_tasks = env_int("TLFEA_RANGE_TASKS", t.range_tasks, 1, 1 << 20);
   t.range_values = env_int("TLFEA_RANGE_VALUES", t.range_values, 1, 12 * 1024);

@@ -25,6 +25,7 @@ namespace tlfea {
 
 constexpr int kStageThreads = 256;     // (element, point) indices per pass-1 workgroup
 constexpr int kMaxRangeNodes = 64;      // nodes per pass-2 workgroup
+constexpr int64_t kRows64MinShell = 4096;  // 3x3x2 shells from which float64 meshes take element rows
 
 // Bytes per (element, node) row of the slot map: padded so that a row is one
 // aligned vector load (T10: 10 ranks in 16 bytes, ANCF: 4 ranks in 4 bytes).
@@ -39,10 +40,11 @@ struct GatherTuning {
   int range_values = 4096;
 };
 // defaults ({4, 768, 2048} for T10 meshes created in mixed precision, whose
-// tangent takes the element-row path, {8, 768, 4096} for ANCF meshes that do
-// (500,000 mixed beams: pass 2 with 4 waves 684 us, 8 waves 619; 65,536 mixed shells
-// 274 / 250, float64 373 / 360), else {4, 768, 4096}), overridden by
-// TLFEA_GATHER_WAVES / TLFEA_RANGE_TASKS / TLFEA_RANGE_VALUES when set
+// tangent takes the element-row path, {8, 768, 4096} for ANCF meshes in mixed
+// precision or large ones whose float64 tangent takes the rows (500,000 mixed
+// beams: pass 2 with 4 waves 684 us, 8 waves 619; 65,536 mixed shells 274 / 250,
+// float64 373 / 360), else {4, 768, 4096}), overridden by TLFEA_GATHER_WAVES /
+// TLFEA_RANGE_TASKS / TLFEA_RANGE_VALUES when set
 struct Mesh;
 GatherTuning gather_tuning(const Mesh& m);
 // a range's LDS segment (CSR values + force rows) must stay below this
