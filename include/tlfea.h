@@ -391,7 +391,9 @@ int tlfea_get_runtime_flags(tlfea_mesh_t mesh, uint32_t* flags);
  * mixed precision or of 3,000 elements or more (3x3x2 shells in float64: 4,096),
  * and {4, 768, 4096} otherwise
  * (environment TLFEA_GATHER_WAVES / TLFEA_RANGE_TASKS / TLFEA_RANGE_VALUES
- * override it when the pattern is built).
+ * override it when the pattern is built).  Of a default shape's eight waves,
+ * passes over float64 point records and the force alone use four where there are
+ * more than 256 ranges.
  * ------------------------------------------------------------------------- */
 typedef struct {
   int32_t waves;        /* waves of 64 lanes per workgroup, 1 .. 8 */

@@ -2241,12 +2241,13 @@ int launch_nodes_rule(const Mesh& m, const void* stage, double* f, double* vals,
   g.inv_h = mt.inv_h;
   g.row_off_u = mt.row_off_u;
   g.inc_cap = (int)((m.max_range_inc + 15) / 16 * 16);
+  const int waves = record_waves(m.tune, m.n_ranges);
   const size_t lds = sizeof(double) * (want_k ? m.max_range_values : m.max_range_rows) + g.inc_cap +
-                     (size_t)m.tune.waves * (krec ? (sym ? wave_buf_bytes<Rule, R, true, sizeof(R) == 8>()
-                                                         : wave_buf_bytes<Rule, R, true>())
-                                                  : wave_buf_bytes<Rule, R, false>()) +
+                     (size_t)waves * (krec ? (sym ? wave_buf_bytes<Rule, R, true, sizeof(R) == 8>()
+                                                  : wave_buf_bytes<Rule, R, true>())
+                                           : wave_buf_bytes<Rule, R, false>()) +
                      (mt.row_off_u ? upper_table_bytes(m) : 0);
-  const dim3 grid((unsigned)m.n_ranges), blk(64 * m.tune.waves);
+  const dim3 grid((unsigned)m.n_ranges), blk(64 * waves);
 #define TLFEA_GATHER_S(F, K, A, KR, SY)                                              \
   do {                                                                               \
     if (int rc = allow_lds(k_gather<Rule, R, F, K, A, KR, SY>, lds)) return rc;      \
@@ -2397,7 +2398,7 @@ int launch_rows_mc_nodes(const Mesh& m, double* f, double* vals, bool accum, hip
   g.inc_cap = (int)((m.max_range_inc + 15) / 16 * 16);
   const size_t lds = sizeof(double) * (want_k ? m.max_range_values : m.max_range_rows) + g.inc_cap +
                      (mt.row_off_u ? upper_table_bytes(m) : 0);
-  const dim3 grid((unsigned)m.n_ranges), blk(64 * m.tune.waves);
+  const dim3 grid((unsigned)m.n_ranges), blk(64 * (want_k ? m.tune.waves : record_waves(m.tune, m.n_ranges)));
 #define TLFEA_GATHER(F, K, A)                                                   \
   do {                                                                          \
     if (int rc = allow_lds(k_gather_rows_mc<Rule, R, F, K, A>, lds)) return rc;    \
@@ -2446,9 +2447,10 @@ int launch_batch_rule(const GatherTuning& tu, const BatchArgs& b, int n_ranges, 
   if (b.n_blocks > 0)
     hipLaunchKernelGGL((k_stage_batch<Rule, R>), dim3((unsigned)b.n_blocks), dim3(kStageThreads), 0, s, b);
   TLFEA_HIP_CHECK(hipGetLastError());
-  const size_t lds_all = lds + b.inc_cap + (size_t)tu.waves * wave_buf_bytes<Rule, R, true>();
+  const int waves = record_waves(tu, n_ranges);
+  const size_t lds_all = lds + b.inc_cap + (size_t)waves * wave_buf_bytes<Rule, R, true>();
   if (int rc = allow_lds(k_gather_batch<Rule, R>, lds_all)) return rc;
-  hipLaunchKernelGGL((k_gather_batch<Rule, R>), dim3(n_ranges), dim3(64 * tu.waves), lds_all, s, b);
+  hipLaunchKernelGGL((k_gather_batch<Rule, R>), dim3(n_ranges), dim3(64 * waves), lds_all, s, b);
   TLFEA_HIP_CHECK(hipGetLastError());
   return TLFEA_OK;
 }

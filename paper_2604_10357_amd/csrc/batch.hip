@@ -457,7 +457,7 @@ TLFEA_API int tlfea_batch_assemble_loop(tlfea_batch_t b, const double* d_q, cons
 TLFEA_API int tlfea_batch_set_gather_shape(tlfea_batch_t b, const tlfea_gather_shape* shape) {
   if (!b || !shape) return TLFEA_ERR_INVALID;
   if (!batch_current(b)) return TLFEA_ERR_INVALID;
-  return batch_set_shape(b, tlfea::GatherTuning{shape->waves, shape->range_tasks, shape->range_values});
+  return batch_set_shape(b, tlfea::GatherTuning{shape->waves, shape->range_tasks, shape->range_values, true});
 }
 
 TLFEA_API int tlfea_batch_get_gather_shape(tlfea_batch_t b, tlfea_gather_shape* shape, int64_t* n_ranges) {

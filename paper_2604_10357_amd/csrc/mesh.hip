@@ -641,7 +641,7 @@ TLFEA_API int tlfea_get_runtime_flags(tlfea_mesh_t mesh, uint32_t* flags) {
 }
 
 static tlfea::GatherTuning shape_in(const tlfea_gather_shape& s) {
-  return tlfea::GatherTuning{s.waves, s.range_tasks, s.range_values};
+  return tlfea::GatherTuning{s.waves, s.range_tasks, s.range_values, true};
 }
 
 static void shape_out(const tlfea::GatherTuning& t, tlfea_gather_shape* s) {

@@ -433,7 +433,9 @@ GatherTuning gather_tuning(const Mesh& m) {
   const bool shell332 = m.elem_type == TLFEA_ANCF3443 && m.gl[0] == 3;
   if (m.elem_type != TLFEA_T10 && (m.precision == TLFEA_MIXED || m.n_elem >= (shell332 ? kRows64MinShell : 3000)))
     t.waves = 8;
-  t.waves = env_int("TLFEA_GATHER_WAVES", t.waves, 1, 8);
+  const int waves = env_int("TLFEA_GATHER_WAVES", 0, 1, 8);
+  t.chosen = waves > 0;
+  if (t.chosen) t.waves = waves;
   t.range_tasks = env_int("TLFEA_RANGE_TASKS", t.range_tasks, 1, 1 << 20);
   t.range_values = env_int("TLFEA_RANGE_VALUES", t.range_values, 1, 12 * 1024);
   return t;
@@ -504,7 +506,7 @@ std::vector<GatherTuning> gather_candidates() {
   std::vector<GatherTuning> c;
   for (int w : {2, 4, 8})
     for (int t : {384, 768, 1536})
-      for (int v : {2048, 4096, 8192}) c.push_back(GatherTuning{w, t, v});
+      for (int v : {2048, 4096, 8192}) c.push_back(GatherTuning{w, t, v, true});
   return c;
 }
 

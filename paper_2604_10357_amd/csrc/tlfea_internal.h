@@ -38,7 +38,16 @@ struct GatherTuning {
   int waves = 4;
   int range_tasks = 768;
   int range_values = 4096;
+  bool chosen = false;  // by the caller, the autotuner or the environment
 };
+// Waves of a pass 2 over point records, or over row blocks for the force alone.  The
+// eight of a default shape are for the tangent's row blocks; with more ranges than
+// CUs, records and the force alone take four (float64 records of 576 3x3x2 shells, 208
+// ranges, 27 us with eight waves and 36 with four, of 1,024, 363 ranges, 43 / 41, of
+// 1,600 59 / 50; the force alone of 400,000 beams 112 / 77).
+inline int record_waves(const GatherTuning& t, int64_t n_ranges) {
+  return t.chosen || n_ranges <= 256 ? t.waves : std::min(t.waves, 4);
+}
 // defaults ({4, 768, 2048} for T10 meshes created in mixed precision, whose
 // tangent takes the element-row path, {8, 768, 4096} for ANCF meshes in mixed
 // precision or large ones whose float64 tangent takes the rows (500,000 mixed
