@@ -145,8 +145,8 @@ __device__ __forceinline__ R record_value_sym(const HatOut<R>& h) {
   }
 }
 
-// Where the slot (i, k) of a task lies in an element-row record (full or
-// symmetric layout), and whether its Ahat block is read transposed.
+// Where the slot (i, k) of a task lies in a point record (full or symmetric
+// layout), and whether its Ahat block is read transposed.
 struct SlotRef {
   int off;  // first Ahat value
   int p;    // Phat_ik
@@ -161,37 +161,6 @@ __device__ __forceinline__ SlotRef slot_ref(int i, int k) {
     const int sl = lo == 0 ? hi : lo == 1 ? hi + 2 : 5;
     const bool tr = i > k;
     return {kSlot * sl, tr ? 6 * kSlot + i + k - 1 : kSlot * sl + 9, tr};
-  }
-}
-
-// The ten values of a task's slot at one point of a record in LDS: Ahat_imkn
-// at 3 m + n, then Phat_ik.
-template <bool SYM>
-__device__ __forceinline__ void read_slot(const float* r, const SlotRef& sr, float (&v)[10]) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  if constexpr (!SYM) {
-#pragma unroll
-    for (int x = 0; x < 5; ++x) {
-      const f2 w = *reinterpret_cast<const f2*>(r + sr.off + 2 * x);
-      v[2 * x] = w[0];
-      v[2 * x + 1] = w[1];
-    }
-  } else {
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const f2 w = *reinterpret_cast<const f2*>(r + sr.off + 2 * x);
-      v[2 * x] = w[0];
-      v[2 * x + 1] = w[1];
-    }
-    v[8] = r[sr.off + 8];
-    v[9] = r[sr.p];
-    const float a1 = v[1], a2 = v[2], a5 = v[5];
-    v[1] = sr.tr ? v[3] : a1;
-    v[3] = sr.tr ? a1 : v[3];
-    v[2] = sr.tr ? v[6] : a2;
-    v[6] = sr.tr ? a2 : v[6];
-    v[5] = sr.tr ? v[7] : a5;
-    v[7] = sr.tr ? a5 : v[7];
   }
 }
 
@@ -1588,62 +1557,60 @@ __device__ __forceinline__ void elem_rows_mc_tile(const AsmArgs& a, const int32_
   __syncthreads();
   if constexpr (MF) {
     rows_mc_mfma_contract<Rule, EB, SYM>(a, incpos, rows, e0, ne, rec, dn);
-    return;
-  }
-  if constexpr (SYM) {
+  } else if constexpr (SYM) {
     rows_mc_sym_contract<Rule, EB>(a, incpos, rows, e0, ne, rec, dn);
-    return;
-  }
-  // 2. a lane per task (element, coefficient a, row i, component k), tasks in
-  //    block order; the point loop is uniform across the workgroup, so the
-  //    gradients dN_b(q) of the columns come through the scalar cache
-  const int ntask = ne * NEN * 9;
-  for (int t0 = 0; t0 < EB * NEN * 9; t0 += kRowsMcThreads) {
-    const int t = t0 + tid;
-    const bool on = t < ntask;
-    const int tt = on ? t : ntask - 1;
-    const int le = tt / (NEN * 9), r9 = tt - le * NEN * 9, al = r9 / 9, s = r9 - 9 * al;  // s = 3 i + k
-    const int k = s % 3;
-    float acc[NEN];
+  } else {
+    // 2. a lane per task (element, coefficient a, row i, component k), tasks in
+    //    block order; the point loop is uniform across the workgroup, so the
+    //    gradients dN_b(q) of the columns come through the scalar cache
+    const int ntask = ne * NEN * 9;
+    for (int t0 = 0; t0 < EB * NEN * 9; t0 += kRowsMcThreads) {
+      const int t = t0 + tid;
+      const bool on = t < ntask;
+      const int tt = on ? t : ntask - 1;
+      const int le = tt / (NEN * 9), r9 = tt - le * NEN * 9, al = r9 / 9, s = r9 - 9 * al;  // s = 3 i + k
+      const int k = s % 3;
+      float acc[NEN];
 #pragma unroll
-    for (int b = 0; b < NEN; ++b) acc[b] = 0.0f;
-    float facc = 0.0f;
-    const float* recp = rec + le * NQ * RS;
-    const SlotRef sr = slot_ref<SYM>(s / 3, k);
-    static_assert(NQ % kRowsMcUnroll == 0, "point steps tile the rule");
+      for (int b = 0; b < NEN; ++b) acc[b] = 0.0f;
+      float facc = 0.0f;
+      const float* recp = rec + le * NQ * RS + kSlot * s;
+      static_assert(NQ % kRowsMcUnroll == 0, "point steps tile the rule");
 #pragma unroll 1
-    for (int q0 = 0; q0 < NQ; q0 += kRowsMcUnroll) {
-      sfor<0, kRowsMcUnroll>([&](auto uc) __attribute__((always_inline)) {
-        const int qq = q0 + decltype(uc)::value;
-        float v[10];
-        read_slot<SYM>(recp + qq * RS, sr, v);
-        const float* d = dn + 3 * (NEN * qq + al);
-        const float d0 = d[0], d1 = d[1], d2 = d[2];
-        const float t0n = v[0] * d0 + v[3] * d1 + v[6] * d2;
-        const float t1n = v[1] * d0 + v[4] * d1 + v[7] * d2;
-        const float t2n = v[2] * d0 + v[5] * d1 + v[8] * d2;
-        facc += v[9] * (k == 0 ? d0 : k == 1 ? d1 : d2);
+      for (int q0 = 0; q0 < NQ; q0 += kRowsMcUnroll) {
+        sfor<0, kRowsMcUnroll>([&](auto uc) __attribute__((always_inline)) {
+          const int qq = q0 + decltype(uc)::value;
+          Slot<float, true> sv;
+          load_slot<float, true>(recp + qq * RS, sv);
+          const float(&v)[10] = sv.v;
+          const float* d = dn + 3 * (NEN * qq + al);
+          const float d0 = d[0], d1 = d[1], d2 = d[2];
+          const float t0n = v[0] * d0 + v[3] * d1 + v[6] * d2;
+          const float t1n = v[1] * d0 + v[4] * d1 + v[7] * d2;
+          const float t2n = v[2] * d0 + v[5] * d1 + v[8] * d2;
+          facc += v[9] * (k == 0 ? d0 : k == 1 ? d1 : d2);
 #pragma unroll
-        for (int b = 0; b < NEN; ++b)
-          acc[b] += t0n * Rule::dNf_rt(qq, b, 0) + t1n * Rule::dNf_rt(qq, b, 1) + t2n * Rule::dNf_rt(qq, b, 2);
-      });
-    }
-    if (on) {
-      double sc[4];
-      element_scales<Rule>(a, e0 + le, sc);
-      const float s_a = (float)sc[al & 3];
-      const int64_t pos = incpos[(e0 + le) * NPN + (al >> 2)];
-      const int r = 3 * (al & 3) + s / 3;  // block row (kind, i)
-      float* blk = rows + pos * BLK;
-      f32x4* outv = reinterpret_cast<f32x4*>(blk + (3 * r + k) * NEN);
-#pragma unroll
-      for (int u = 0; u < NEN / 4; ++u) {
-        f32x4 w;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) w[x] = acc[4 * u + x] * s_a * (float)sc[x];  // b = 4 u + x: kind x
-        outv[u] = w;
+          for (int b = 0; b < NEN; ++b)
+            acc[b] += t0n * Rule::dNf_rt(qq, b, 0) + t1n * Rule::dNf_rt(qq, b, 1) + t2n * Rule::dNf_rt(qq, b, 2);
+        });
       }
-      blk[36 * NEN + 3 * r + k] = facc * s_a;
+      if (on) {
+        double sc[4];
+        element_scales<Rule>(a, e0 + le, sc);
+        const float s_a = (float)sc[al & 3];
+        const int64_t pos = incpos[(e0 + le) * NPN + (al >> 2)];
+        const int r = 3 * (al & 3) + s / 3;  // block row (kind, i)
+        float* blk = rows + pos * BLK;
+        f32x4* outv = reinterpret_cast<f32x4*>(blk + (3 * r + k) * NEN);
+#pragma unroll
+        for (int u = 0; u < NEN / 4; ++u) {
+          f32x4 w;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) w[x] = acc[4 * u + x] * s_a * (float)sc[x];  // b = 4 u + x: kind x
+          outv[u] = w;
+        }
+        blk[36 * NEN + 3 * r + k] = facc * s_a;
+      }
     }
   }
 }
