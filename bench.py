@@ -288,11 +288,13 @@ def bench_mesh(args, torch, wl, wname):
     achieved = B / (ms * 1e-3) / 1e9
     traffic = measured_traffic(wname, args.precision, tuning["gather_shape"])
     kname = {1: "T10", 2: "ANCF3443", 3: "ANCF3243"}[wl.mesh.elem_type]
-    # the tangent in mixed precision takes the element-row kernels
+    # the element-row kernels: mixed precision, and in float64 the forms that
+    # tlfea_assemble_points names
     mixed = args.precision == "mixed"
     damped = bool(wl.material.kv_eta or wl.material.kv_lambda)
     rows_path = os.environ.get("TLFEA_ELEMENT_ROWS") != "0" and (
-        mixed or (damped and n_el >= 49152 if kname == "T10" else n_el >= 3000))
+        mixed or n_el >= ((49152 if damped else float("inf")) if kname == "T10" else
+                          (4 if damped else 8) if kname == "ANCF3243" else 4096 if wl.mesh.gl[2] == 2 else 0))
     mat = "mooney_rivlin" if wl.material.kind == 2 else "svk"
     if wl.material.kv_eta or wl.material.kv_lambda:
         mat += "+kelvin_voigt"

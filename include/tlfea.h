@@ -196,12 +196,14 @@ int tlfea_internal_force_noalloc(tlfea_mesh_t mesh, const double* d_q, const dou
                                  void* stream);
 
 /* Kernel forms of the tangent calls below (results equal up to rounding
- * order; Sec. 4.4.2, Eq. tangent_block): in mixed precision, a material
- * without Kelvin-Voigt damping has a symmetric tangent, and the element pass
- * then contracts only the slots i <= k of every point's tangent and stores the
- * others by transposition; the shell's contraction runs on the matrix cores.
- * Environment TLFEA_SYM_RECORDS=0 and TLFEA_MC_MFMA=0 (read once per process)
- * keep the full contraction and the vector form, for comparisons. */
+ * order; Sec. 4.4.2, Eq. tangent_block): a material without Kelvin-Voigt
+ * damping has a symmetric tangent; where the element pass contracts the points
+ * (tlfea_assemble_points) it then takes only the slots i <= k of every point's
+ * tangent and stores the others by transposition (in float64 the shells'), and
+ * the shell's contraction runs on the matrix cores in both precisions.
+ * Environment TLFEA_SYM_RECORDS=0 (read once per process) keeps the full
+ * contraction, TLFEA_MC_MFMA=0 the vector form of the mixed shell, for
+ * comparisons. */
 
 /* CSR values of h * df/dq + df/dqdot = d f_int(q_n + h v, v) / dv -> d_vals (nnz). */
 int tlfea_tangent(tlfea_mesh_t mesh, const double* d_q, const double* d_qdot, double h,
@@ -241,18 +243,22 @@ int tlfea_assemble_upper(tlfea_mesh_t mesh, const double* d_q, const double* d_q
  * other work between them (e.g. pass 1 of the next mesh) or time them:
  *   tlfea_assemble_points: per element and quadrature point, the constitutive
  *     update (Sec. 4.3, Stage 1), then, into the mesh's work buffer, one of:
- *     with the tangent in mixed precision, each element's rows of K_e
+ *     with the tangent in mixed precision, and in float64 for 4x4x3 shells,
+ *     beams (from 4 damped or 8 undamped elements), 3x3x2 shells from 4,096
+ *     elements and damped T10 meshes from 49,152, each element's rows of K_e
  *     (alpha dP/dF + beta dP/dFdot contracted over its points, Eq.
  *     tangent_block) and its force, one block per (element, node) incidence;
- *     with the tangent in float64, per point the stress and the tangent in
+ *     with any other tangent in float64, per point the stress and the tangent in
  *     parent coordinates with the quadrature volume folded in; without the
  *     tangent (want_tangent = 0), each element's force, one block per
- *     incidence.  Allocates the buffer when it is too small (synchronising).
- *     In float64 the per-element rows of a large mesh may need more than the
- *     per-point form; a buffer that already holds the latter (the mesh's tangent
- *     ran undamped, or in mixed precision) is kept and the per-point form taken,
- *     so that tlfea_mesh_set_material and tlfea_mesh_set_precision cause no
- *     allocation there; likewise where the device has no memory for the rows.
+ *     incidence.  Allocates the buffer when it is too small (synchronising): per
+ *     element at most 3.8 KB for T10 (the damped float64 rows 7.7), 9.2 for the
+ *     beam, 13.8 for the 3x3x2 shell (its float64 rows 19.6) and 36.9 for the
+ *     4x4x3 one.  Where the float64 rows are the larger form, a buffer that
+ *     already holds the per-point form (the mesh's tangent ran undamped, or in
+ *     mixed precision) is kept and that form taken, so that
+ *     tlfea_mesh_set_material and tlfea_mesh_set_precision cause no allocation
+ *     there; likewise where the device has no memory for the rows.
  *   tlfea_assemble_nodes: per node, the sums of Eqs. fint_local / fint_global
  *     and Eq. tangent_block over the incident elements, written to d_f and / or
  *     d_vals (either may be NULL; d_vals needs want_tangent = 1); accumulate

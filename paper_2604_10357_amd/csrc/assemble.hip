@@ -1263,6 +1263,8 @@ __global__ __launch_bounds__(512) void k_gather_rows_batch_lpt(BatchArgs b, cons
 // then the parts P^_ik dN_a,k s_a of f_a,i at 36 NEN + 3 r + k (the three
 // parts of a row are added in pass 2).
 constexpr int kRowsMcThreads = 128;
+// Three points a step instead of two: undamped, 500,000 beams 1,337 -> 1,327 us and
+// 50,000 152.9 -> 151.1; the full form (damped) 1,772 -> 1,769 and 198.2 -> 200.3.
 #ifndef TLFEA_ROWS_MC_UNROLL
 #define TLFEA_ROWS_MC_UNROLL 3
 #endif
@@ -1741,14 +1743,17 @@ __device__ __forceinline__ void rows64_vector(const RowsOut<Rule, EB>& ro, doubl
 // One row component i of the shell's elements on the matrix cores: a wave takes
 // the 16 x 16 tile K^(ik)_ab = sum over (q, n) of T_n(q)[a] dN_b,n(q), T_n(q)[a] =
 // sum_m Ahat_q,imkn dN_a,m(q), as 16x16x4 products over four points per n (the
-// point axis is padded to a multiple of four with zeros).  Lane l is coefficient
-// l % 16 of both sides at point l / 16 of the four: the three gradients it reads
+// point axis is padded to a multiple of four with zeros).  Lane l takes position
+// p = l % 16 of both sides at point l / 16 of the four: the three gradients it reads
 // serve as A's factor and as B, and a slot value is read once per row of 16 lanes
 // and passed along the row, so a step reads four doubles per lane for three
 // products (the vector form: thirteen for 57 multiply-adds, bound by LDS; pass 1 of 65,536
 // 3x3x2 shells 835 us, so 611).  For an undamped material the slots i <= k alone
 // are multiplied and stored a second time, transposed.
-// Lane l then holds K^(ik)[l / 16 + 4 r][l % 16], r < 4: node r, kind l / 16.
+// Position p stands for coefficient 4 (p % 4) + p / 4.  The product leaves lane l the
+// rows at positions l / 16 + 4 r, r < 4, of column position l % 16: coefficients
+// 4 (l / 16) + r, so a lane holds the four kinds of node l / 16, whose transposed
+// entries are consecutive in a block.
 template <class Rule, bool SYM, int I, int EB>
 __device__ __forceinline__ void rows64_matrix(const RowsOut<Rule, EB>& ro, double* __restrict__ rows, int ne,
                                               const double* rec, const double* dn) {
@@ -2440,8 +2445,8 @@ static bool rows_on() {
 // float64 element rows (T10): pass 1 has one wave per SIMD and writes 3.7 GB of
 // blocks for 480,000 elements, pass 2 reads each once; point records are half
 // that size, but pass 2 reads them 6.5 times.  Whole call, rows against records:
-// 30,000 elements 148 / 144 us, 60,000 271 / 311, 480,000 2,070 / 2,382: the line
-// is at four rounds of 1,024 waves.  Undamped meshes keep the symmetric records
+// 30,000 elements 148 / 144 us, 49,200 247 / 245, 49,800 249 / 249, 60,000 271 / 311,
+// 480,000 2,070 / 2,382: the line is where the fifth round of 1,024 waves starts.  Undamped meshes keep the symmetric records
 // (480,000: 2,014 / 1,795).
 constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
 
@@ -2455,7 +2460,7 @@ constexpr int64_t kRows64MinElems = 4 * 1024 * kRowElems;
 // one element 107 / 181, 40 of 100 104 / 113.
 constexpr int64_t kRows64MinShellBatch = 3000;
 
-// The 4x4x3 shell, whose records are the larger (35 KB an element against 19.6),
+// The 4x4x3 shell, whose records are the larger (36.9 KB an element against 19.6),
 // takes rows at every size (1 element 18 / 40 us, 64 39 / 71, 10,000 257 / 434).
 //
 // float64 element rows of the beam: one wave's chain takes 14 us, which the records

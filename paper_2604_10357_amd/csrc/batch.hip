@@ -33,7 +33,7 @@ struct tlfea_batch_s {
   size_t ranges_cap = 0;             // BatchRange entries d_ranges holds
   tlfea::GatherTuning tune;          // pass-2 launch shape the ranges are cut for
   int64_t n_points = 0, n_blocks = 0;
-  int rows = 0;                      // element-row path (mixed; persistent schedule for T10)
+  int rows = 0;                      // element-row path (use_rows_batch)
   int64_t n_inc = 0, n_rblocks = 0;  // its row blocks and pass-1 workgroups
   int row_tile = 1;                  // elements of a pass-1 workgroup
   int rows_nt = 0;                   // T10: the row blocks are stored past the caches

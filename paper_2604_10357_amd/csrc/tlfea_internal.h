@@ -174,7 +174,7 @@ struct Mesh {
   int32_t* d_inc_off = nullptr;   // n_pnodes + 1, node -> incident elements
   int32_t* d_inc = nullptr;       // (element << 4) | local node index, sorted by element per node
   int32_t* d_ranges = nullptr;    // n_ranges + 1 node boundaries
-  int32_t* d_incpos = nullptr;    // T10: incidence position of every (element, local node)
+  int32_t* d_incpos = nullptr;    // incidence position of every (element, local node)
   uint8_t* d_rank_inc = nullptr;  // T10: slot-map rows in incidence order (16 bytes each)
   std::vector<int32_t> h_ranges;
   int n_ranges = 0;
@@ -186,9 +186,8 @@ struct Mesh {
   std::vector<int32_t> h_adj_off;
   void* d_stage = nullptr;        // pass-1 records
   size_t stage_cap = 0;
-  int staged = 0;                 // what the last pass 1 left: 0 none, 1 force records, 2 force + tangent,
-                                  // 3 element row blocks, 4 element force blocks
-                                  // records, 3 element row blocks (force + tangent)
+  int staged = 0;                 // what the last pass 1 left: 0 none, 1 force records, 2 force + tangent
+                                  // records, 3 element row blocks (force + tangent), 4 element force blocks
   int staged_precision = -1;
   bool staged_sym = false;        // point records of the last pass 1 in the symmetric float64 layout
 
@@ -286,7 +285,7 @@ struct BatchArgs {
   int64_t n_rblocks;  // pass-1 workgroups of the element-row path
   int row_tile;       // T10: elements of each (ANCF tiles have a fixed size)
   int nt;             // T10: the row blocks are stored past the caches
-  int rows;           // 1: element-row path (T10, mixed), 0: per-point records
+  int rows;           // 1: element-row path, 0: per-point records
   void* stage;
   const double* q;
   const double* qdot;
@@ -315,20 +314,21 @@ int batch_lpt_occupancy(int tile_elems, bool rows_nt, int waves, size_t lds_all,
 
 MatParams make_params(int material, const double* params, double eta, double lam_v);
 
-// bytes of pass-1 records for a mesh / per record
-// Element-row path: the tangent in mixed precision, every element type, and of
-// large damped T10 meshes in float64 (the environment variable
-// TLFEA_ELEMENT_ROWS=0 switches it off).  Pass 1 then leaves one row block per
-// incidence instead of per-point records.
+// Element-row path: the tangent in mixed precision, every element type, and in
+// float64 that of 4x4x3 shells, of beams but a few, of large 3x3x2 shell meshes and
+// of large damped T10 meshes whose work buffer takes the rows (the environment
+// variable TLFEA_ELEMENT_ROWS=0 switches it off).  Pass 1 then leaves one row block
+// per incidence instead of per-point records.
 bool use_rows(const Mesh& m, bool want_k);
 // the same for a member of a batch of n_elem elements in all (full tangent
 // layout, whatever the material)
 bool use_rows_batch(const Mesh& m, int64_t n_elem);
 bool point_records_sym(const Mesh& m, bool want_k);
-// Force-only path (every element type; TLFEA_FORCE_BLOCKS=0 switches it off):
-// pass 1 leaves one float-or-double force block of 3 mc values per incidence.
+// Force-only path (every element type; TLFEA_FORCE_BLOCKS=0 switches it off, but not
+// in the first-order solver, whose gradient sums the blocks itself): pass 1 leaves
+// one float-or-double force block of 3 mc values per incidence.
 bool use_force_blocks(const Mesh& m, bool want_k);
-size_t stage_bytes(const Mesh& m, bool want_k);
+size_t stage_bytes(const Mesh& m, bool want_k);  // work buffer of a pass 1 of the mesh
 size_t stage_bytes_min(const Mesh& m, bool want_k);  // the same where memory is short (the point records' in float64)
 size_t stage_record_bytes(int precision);
 int lpt_tile_elems();      // elements per item of the persistent batch schedule (the default)
