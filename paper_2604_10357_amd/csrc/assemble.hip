@@ -749,11 +749,14 @@ template <typename R>
 constexpr int row_min_waves() { return sizeof(R) == 4 ? 2 : 1; }
 // Row blocks up to this size in all go through the caches, where pass 2 finds them
 // (the memory-side cache holds 256 MB); larger ones are stored past them, which
-// pass 1 gains from.  Whole call, through / past, of n damped (undamped) elements:
-// 18,000 52 / 55 (51 / 54) us, 30,000 80 / 86 (82 / 87), 33,000 85 / 90 (103 / 93),
-// 36,000 99 / 93 (107 / 100), 480,000 1,194 / 1,134 (1,224 / 1,181): the line is at
-// 32,768 elements.
-constexpr size_t kCachedRowBytes = (size_t)120 << 20;
+// pass 1 gains from.  Whole call, through / past, of damped elements: 18,000 59 / 60
+// us, 21,600 65 / 67, 24,000 71 / 70, 30,000 100 / 97, 36,000 116 / 106 where other
+// meshes' calls lie between two of one (back to back on one mesh 30,000 80 / 86,
+// 33,000 85 / 90, 36,000 99 / 93): the line is at 24,576 elements.  Undamped ones
+// gain less from it, 21,600 70 / 72, 24,000 75 / 75, 30,000 104 / 101 (back to back
+// 82 / 87, 33,000 103 / 93): 32,768 elements, below which neither use loses against
+// the 105 (81) us of 30,000 elements before either store.
+constexpr size_t kCachedRowBytes = (size_t)90 << 20, kCachedSymRowBytes = (size_t)120 << 20;
 // Damped float32 tiles up to this many take a workgroup for each row component: two
 // waves a SIMD.  Whole call, in one / in three workgroups a tile: 6 elements 15.4 /
 // 11.4 us, 270 17.5 / 13.2, 600 17.2 / 15.4, 1,020 18.1 / 20.1 (a tile each).
@@ -2483,7 +2486,7 @@ static size_t rows_bytes(const Mesh& m) {
   return (size_t)m.n_elem * m.n_pn * (m.elem_type == TLFEA_T10 ? kRowBlk : 36 * m.n_en + 36) * r;
 }
 
-bool rows_past_caches(size_t bytes) { return bytes > kCachedRowBytes; }
+bool rows_past_caches(size_t bytes, bool sym) { return bytes > (sym ? kCachedSymRowBytes : kCachedRowBytes); }
 
 static size_t record_bytes(const Mesh& m) { return (size_t)m.n_elem * m.n_qp * stage_record_bytes(m.precision); }
 
@@ -2592,7 +2595,7 @@ int launch_points(const Mesh& m, const AsmArgs& a, bool want_k, hipStream_t s) {
     if (blocks > INT32_MAX) return TLFEA_ERR_TOO_LARGE;
     if (blocks > 0) {
       const dim3 grid((unsigned)blocks);
-      const bool nt = rows_past_caches(rows_bytes(m));
+      const bool nt = rows_past_caches(rows_bytes(m), sym);
       if (sym)
         hipLaunchKernelGGL((nt ? k_elem_rows_sym<RuleT10, true> : k_elem_rows_sym<RuleT10, false>), grid,
                            dim3(kSymThreads), 0, s, a, tile, m.d_incpos, (float*)m.d_stage);

@@ -310,7 +310,7 @@ TLFEA_API int tlfea_batch_create(const tlfea_mesh_t* meshes, int32_t n_bodies, t
   const size_t records = (size_t)b->n_points * tlfea::stage_record_bytes(b->precision);
   const size_t rows = (size_t)b->n_inc * tlfea::row_block_bytes_for(b->elem_type, b->precision);
   const size_t stage = b->rows ? rows : records;
-  b->rows_nt = tlfea::rows_past_caches(rows) ? 1 : 0;
+  b->rows_nt = tlfea::rows_past_caches(rows, false) ? 1 : 0;
   if (hipSetDevice(b->device) != hipSuccess) { delete b; return TLFEA_ERR_HIP; }
   if (hipMalloc(&b->d_bodies, sizeof(BatchBody) * bodies.size()) != hipSuccess ||
       hipMalloc(&b->d_flags, sizeof(uint32_t)) != hipSuccess ||

@@ -334,7 +334,7 @@ size_t stage_record_bytes(int precision);
 int lpt_tile_elems();      // elements per item of the persistent batch schedule (the default)
 size_t row_block_bytes_for(int elem_type, int precision);  // element-row path: bytes per (element, node) row block
 int row_elems_for(int elem_type, int gl0, int precision, int64_t n_elem);  // elements per pass-1 workgroup (n_elem: of the launch)
-bool rows_past_caches(size_t bytes);  // T10 row blocks of this size in all are stored past the caches
+bool rows_past_caches(size_t bytes, bool sym);  // T10 row blocks of this size in all are stored past the caches
 int schedule_tile(int elem_type, int gl0);  // tile_elems reported for a batch that runs per item
 int launch_batch(int elem_type, int gl0, int precision, const GatherTuning& tune, const BatchArgs& b,
                  int n_ranges, size_t lds, hipStream_t s, const BatchSchedule& sc);

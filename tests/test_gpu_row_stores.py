@@ -1,7 +1,7 @@
 """T10 element rows in mixed precision on both sides of the sizes where their launch
-changes: from 32,768 elements on the stores pass the caches (a mesh, a batch per
-item and a batch with the persistent schedule), up to 682 damped tiles each row
-component has a workgroup of its own."""
+changes: from 24,576 damped or 32,768 undamped elements on the stores pass the
+caches (a mesh, a batch per item and a batch with the persistent schedule), up to
+682 damped tiles each row component has a workgroup of its own."""
 import dataclasses
 
 import pytest
@@ -15,8 +15,7 @@ from tests.gpu_util import TOL, cuda, make_mesh, rel_err
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [32768, 32769])
-@pytest.mark.parametrize("damped", [True, False])
+@pytest.mark.parametrize("damped,n", [(True, 24576), (True, 24577), (False, 32768), (False, 32769)])
 def test_rows_through_and_past_the_caches(damped, n):
     print(f"[gpu] row stores damped={damped} {n}", flush=True)
     mat = W.Material(W.MOONEY_RIVLIN, (2e5, 5e4, 1e8), *((1e3, 7e2) if damped else ()))
