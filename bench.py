@@ -45,7 +45,7 @@ def contraction_flop(wl):
 # committed counter reports: file and the two kernels of the mixed call, per workload
 TRAFFIC = {
     "t10_beam": ("hbm_traffic_t10_beam_200x20x20_mixed.json",
-                 ("k_elem_rows<RuleT10, float>", "k_gather_rows<float, true, true, false>")),
+                 ("k_elem_rows<RuleT10, float, true, false>", "k_gather_rows<float, true, true, false>")),
     "ancf_beam": ("hbm_traffic_ancf3243_chain_500000_mixed.json",
                   ("k_elem_rows_mc<RuleBeam, true, false>", "k_gather_rows_mc<RuleBeam, float, true, true, false>")),
 }

@@ -237,8 +237,8 @@ __device__ __forceinline__ void vjp_finalize(const double* __restrict__ gpart, i
 // What follows the element kernel, in one launch: workgroup 0 finalizes the
 // parameters' gradient (its chain of loads runs beside the others), then n_sum
 // workgroups sum the q blocks of the nodes' incidences, then as many the qdot
-// blocks; a gradient that is not asked for has no workgroups.  Forward and
-// backward of 112,398 elements with all three: 152 us with three launches, 144.
+// blocks; a gradient that is not asked for has no workgroups.  For 10,000 shells with
+// all three: 4.6 + 4.6 + 3.9 us of three kernels in turn, 4.7 in one.
 struct VjpTail {
   const int32_t* inc_off;
   const double *bq, *bqd, *gpart, *d_params;
